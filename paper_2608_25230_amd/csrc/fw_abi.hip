@@ -97,6 +97,8 @@ struct DenseTopkWs {
     float *z, *row_m, *row_l;
     uint32_t *thr_key;
     int32_t *thr_cut;
+    int splits;           // key ranges of the tier sums
+    float *part, *part_m; // their partial sums, splits > 1
     size_t bytes;
 };
 
@@ -109,6 +111,21 @@ DenseTopkWs dense_topk_layout(const fw_rows *rows, int n_ks, void *ws) {
     w.row_l = c.take<float>(R);
     w.thr_key = c.take<uint32_t>(R * n_ks);
     w.thr_cut = c.take<int32_t>(R * n_ks);
+    // Partial sums only as far as a call that fits the static scratch array
+    // without them still fits it with them.
+    const size_t base = c.size(), nt = (size_t)n_ks + 1;
+    const auto extra = [&](int s) {
+        return fw::align_up((size_t)s * R * nt * rows->d * sizeof(float), 256) +
+               fw::align_up((size_t)s * R * nt * sizeof(float), 256);
+    };
+    w.splits = fw::tiers_splits(rows->dtype, rows->H, rows->G, rows->n);
+    while (w.splits > 1 && base <= FW_NOALLOC_SCRATCH_BYTES && base + extra(w.splits) > FW_NOALLOC_SCRATCH_BYTES)
+        --w.splits;
+    w.part = w.part_m = nullptr;
+    if (w.splits > 1) {
+        w.part = c.take<float>((size_t)w.splits * R * nt * rows->d);
+        w.part_m = c.take<float>((size_t)w.splits * R * nt);
+    }
     w.bytes = c.size();
     return w;
 }
@@ -229,8 +246,8 @@ fw_status dense_topk_launch(const fw_rows *rows, const fw::KsArg &k, float *o, f
         e = fw::launch_select(w.z, H * G, n, k, w.row_m, w.row_l, w.thr_key, w.thr_cut, topk_idx,
                               kmax, st);
     if (e == hipSuccess)
-        e = fw::launch_tiers(rows->dtype, rows->v, w.z, w.row_m, w.row_l, w.thr_key, w.thr_cut, H,
-                             G, n, d, k, o, o_s, gap, dropped, st);
+        e = fw::launch_tiers(rows->dtype, rows->v, w.z, w.row_m, w.thr_key, w.thr_cut, H, G, n, d, k, o, o_s, gap,
+                             dropped, w.splits, w.part, w.part_m, st);
     return hip_status(e, "fw_dense_topk");
 }
 
