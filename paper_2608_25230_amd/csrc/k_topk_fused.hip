@@ -22,7 +22,6 @@
 // more than 128 logits sharing the threshold bin) are listed and recomputed by
 // a one-row-per-workgroup fallback that selects by radix over the exact keys.
 #include "fw_internal.hpp"
-#include "select.hpp"
 #include "topk_fused.hpp"
 
 namespace fw {
@@ -855,22 +854,30 @@ __global__ void fused_clear_kernel(int32_t *flag_count) {
 }
 
 // ---------------------------------------------------------------------------
-// fallback for listed rows: one workgroup per row, exact radix selection
+// fallback for listed rows: one workgroup of 16 waves per row.  Usually a
+// handful of rows of tens of thousands, so what counts is one row's latency:
+// half a key's row in flight per thread for the logits (same sums in column
+// order), one sort of (logit, index) keys in LDS that gives every budget's
+// threshold and the rank order, and the tier sums by 64 groups of 16 lanes,
+// eight keys in flight each.  A few rows of 4096 keys and three budgets:
+// 100 to 160 us, 985 us with 4 waves per row and a radix selection per budget.
 // ---------------------------------------------------------------------------
+constexpr int XT = 1024;  // threads per row
+
 template <int NK>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(XT)
 fused_fixup_kernel(FusedArgs a, int32_t *topk_idx) {
-    constexpr int NT = NK + 1;
-    __shared__ float z[4096];
-    __shared__ int hist[256];
-    __shared__ int scan[256];
-    __shared__ int sh[4];
-    __shared__ float redf[256];
-    __shared__ float acc_s[2][NT][FD + 1];   // [key half][tier][column]
-    __shared__ float mass_s[2][NT];
+    constexpr int NT = NK + 1, NW = XT / 64;
+    __shared__ float z[4096];  // logits, then weights
+    __shared__ unsigned char tier_s[4096];
+    __shared__ float redf[NW];
+    __shared__ float mass_s[NW][NT];
     __shared__ float qs[FD];
-    __shared__ unsigned long long sb[4096];   // weights and tiers, then the sort buffer
-    const int tid = threadIdx.x;
+    __shared__ unsigned long long sb[4096];  // sort keys, then the waves' tier sums
+    __shared__ unsigned long long thr[NK];   // each budget's last key
+    static_assert(sizeof(float) * NW * 4 * FD <= sizeof(unsigned long long) * 4096, "tier sums fit the sort buffer");
+    float *acc_s = (float *)sb;  // [wave][tier][column]
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int n = a.n;
     const int count = *a.flag_count;
     for (int li = blockIdx.x; li < count; li += gridDim.x) {
@@ -880,92 +887,155 @@ fused_fixup_kernel(FusedArgs a, int32_t *topk_idx) {
         const uint16_t *qr = a.q + r * FD;
         const uint16_t *kh = a.k + h * (int64_t)n * FD;
         const uint16_t *vh = a.v + h * (int64_t)n * FD;
-        for (int c = tid; c < FD; c += 256) qs[c] = bf16_bits_to_f32(qr[c]);
+        for (int c = tid; c < FD; c += XT) qs[c] = bf16_bits_to_f32(qr[c]);
         __syncthreads();
-        for (int j = tid; j < n; j += 256) {
-            // the key row in 16-byte pieces
+#pragma nounroll
+        for (int j = tid; j < n; j += XT) {
             const uint4 *kr = (const uint4 *)(kh + (int64_t)j * FD);
             float s = 0.f;
-            for (int c8 = 0; c8 < FD / 8; ++c8) {
-                const uint4 x = kr[c8];
-                const uint32_t wd[4] = {x.x, x.y, x.z, x.w};
+#pragma nounroll
+            for (int c0 = 0; c0 < FD / 8; c0 += 8) {
+                uint4 x[8];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    s = fmaf(qs[8 * c8 + 2 * u], __uint_as_float(wd[u] << 16), s);
-                    s = fmaf(qs[8 * c8 + 2 * u + 1], __uint_as_float(wd[u] & 0xFFFF0000u), s);
+                for (int c8 = 0; c8 < 8; ++c8) x[c8] = kr[c0 + c8];
+                const float *qc = qs + 8 * c0;
+#pragma unroll
+                for (int c8 = 0; c8 < 8; ++c8) {
+                    const uint32_t wd[4] = {x[c8].x, x[c8].y, x[c8].z, x[c8].w};
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        s = fmaf(qc[8 * c8 + 2 * u], __uint_as_float(wd[u] << 16), s);
+                        s = fmaf(qc[8 * c8 + 2 * u + 1], __uint_as_float(wd[u] & 0xFFFF0000u), s);
+                    }
                 }
             }
             z[j] = sc * s + (a.bias ? a.bias[j] : 0.f);
         }
         __syncthreads();
         float m = -INFINITY;
-        for (int j = tid; j < n; j += 256) m = fmaxf(m, z[j]);
+        for (int j = tid; j < n; j += XT) m = fmaxf(m, z[j]);
         m = block_reduce(m, redf, OpMax());
         float l = 0.f;
-        for (int j = tid; j < n; j += 256) l += expf(z[j] - m);
+        for (int j = tid; j < n; j += XT) l += expf(z[j] - m);
         l = block_reduce(l, redf, OpSum());
-        uint32_t key[NK];
-        int64_t cut[NK];
-        for (int kk = 0; kk < NK; ++kk) {
-            int rem;
-            radix_select_desc(z, n, a.ks.k[kk], hist, sh, &key[kk], &rem);
-            cut[kk] = nth_tie(z, n, key[kk], rem, scan, sh);
+        // rank order: (logit desc, index asc)
+        int len = 64;
+        while (len < n) len <<= 1;
+        for (int j = tid; j < len; j += XT)
+            sb[j] = j < n ? ((unsigned long long)ord_key(z[j]) << 32) | (0xFFFFFFFFu - (uint32_t)j) : 0ull;
+        __syncthreads();
+        for (int size = 2; size <= len; size <<= 1) {
+            for (int stride = size >> 1; stride > 0; stride >>= 1) {
+                for (int i = tid; i < len / 2; i += XT) {
+                    const int lo = 2 * i - (i & (stride - 1)), hi = lo + stride;
+                    const bool desc = (lo & size) == 0;
+                    const unsigned long long x = sb[lo], y = sb[hi];
+                    if (desc ? (x < y) : (x > y)) { sb[lo] = y; sb[hi] = x; }
+                }
+                __syncthreads();
+            }
         }
-        // every key's weight and tier, then the tier sums: thread (column c,
-        // key half hh) over the keys of its half
-        float *pw = (float *)sb;
-        int *tw = (int *)(pw + 4096);
-        for (int j = tid; j < n; j += 256) {
-            const uint32_t u = ord_key(z[j]);
+        if (tid < NK) thr[tid] = sb[a.ks.k[tid] - 1];
+        if (topk_idx)
+            for (int i = tid; i < a.kmax; i += XT)
+                topk_idx[r * a.kmax + i] = (int32_t)(0xFFFFFFFFu - (uint32_t)(sb[i] & 0xFFFFFFFFull));
+        __syncthreads();
+        for (int j = tid; j < n; j += XT) {
+            const float zj = z[j];
+            const unsigned long long u = ((unsigned long long)ord_key(zj) << 32) | (0xFFFFFFFFu - (uint32_t)j);
             int tier = NK;
+#pragma unroll
             for (int kk = NK - 1; kk >= 0; --kk)
-                if (u > key[kk] || (u == key[kk] && j <= cut[kk])) tier = kk;
-            pw[j] = expf(z[j] - m) / l;
-            tw[j] = tier;
+                if (u >= thr[kk]) tier = kk;
+            z[j] = expf(zj - m) / l;
+            tier_s[j] = (unsigned char)tier;
         }
         __syncthreads();
         {
-            const int c = tid & (FD - 1), hh = tid / FD;
-            const int j0 = hh * (n / 2), j1 = hh ? n : n / 2;
-            float accl[NT], ml[NT];
-            for (int tt = 0; tt < NT; ++tt) { accl[tt] = 0.f; ml[tt] = 0.f; }
-            for (int j = j0; j < j1; ++j) {
-                const float p = pw[j];
-                const int tier = tw[j];
-                const float vv = bf16_bits_to_f32(vh[(int64_t)j * FD + c]);
+            // 16 lanes per key, eight columns each; a group takes every 64th key
+            const int c0 = 8 * (lane & 15), grp = tid >> 4;
+            float accl[NT][8], ml[NT];
 #pragma unroll
-                for (int tt = 0; tt < NT; ++tt)
-                    if (tt == tier) { accl[tt] = fmaf(p, vv, accl[tt]); ml[tt] += p; }
-            }
             for (int tt = 0; tt < NT; ++tt) {
-                acc_s[hh][tt][c] = accl[tt];
-                if (c == 0) mass_s[hh][tt] = ml[tt];
+                ml[tt] = 0.f;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) accl[tt][i] = 0.f;
+            }
+#pragma nounroll
+            for (int j0 = grp; j0 < n; j0 += 64 * 8) {
+                uint4 x[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int j = j0 + 64 * u;
+                    x[u] = j < n ? *(const uint4 *)(vh + (int64_t)j * FD + c0) : make_uint4(0u, 0u, 0u, 0u);
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int j = j0 + 64 * u;
+                    if (j >= n) break;
+                    const float p = z[j];
+                    const int tier = tier_s[j];
+                    const uint32_t wd[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+                    for (int tt = 0; tt < NT; ++tt) {
+                        if (tt == tier) {
+                            ml[tt] += p;
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                accl[tt][2 * i] = fmaf(p, __uint_as_float(wd[i] << 16), accl[tt][2 * i]);
+                                accl[tt][2 * i + 1] = fmaf(p, __uint_as_float(wd[i] & 0xFFFF0000u), accl[tt][2 * i + 1]);
+                            }
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int tt = 0; tt < NT; ++tt) {
+#pragma unroll
+                for (int off = 16; off < 64; off <<= 1) {
+                    ml[tt] += __shfl_xor(ml[tt], off);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) accl[tt][i] += __shfl_xor(accl[tt][i], off);
+                }
+                if (lane < 16) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) acc_s[(w * NT + tt) * FD + c0 + i] = accl[tt][i];
+                }
+                if (lane == 0) mass_s[w][tt] = ml[tt];
             }
         }
         __syncthreads();
-        if (tid < FD) {
-            for (int tt = 0; tt < NT; ++tt) acc_s[0][tt][tid] += acc_s[1][tt][tid];
+        // the waves' sums in order, into wave 0's
+        for (int e = tid; e < NT * FD; e += XT) {
+            float s = 0.f;
+            for (int x = 0; x < NW; ++x) s += acc_s[x * NT * FD + e];
+            acc_s[e] = s;
         }
-        if (tid == 0) {
-            for (int tt = 0; tt < NT; ++tt) mass_s[0][tt] += mass_s[1][tt];
+        float ms[NT];
+#pragma unroll
+        for (int tt = 0; tt < NT; ++tt) {
+            ms[tt] = 0.f;
+            for (int x = 0; x < NW; ++x) ms[tt] += mass_s[x][tt];
         }
         __syncthreads();
         if (tid < 64) {
             const int64_t R = a.H * a.G;
             float mtot = 0.f;
-            for (int tt = 0; tt < NT; ++tt) mtot += mass_s[0][tt];
+#pragma unroll
+            for (int tt = 0; tt < NT; ++tt) mtot += ms[tt];
             for (int c = tid; c < FD; c += 64) {
                 float s = 0.f;
-                for (int tt = 0; tt < NT; ++tt) s += acc_s[0][tt][c];
+                for (int tt = 0; tt < NT; ++tt) s += acc_s[tt * FD + c];
                 if (a.o) a.o[r * FD + c] = s / mtot;
             }
             for (int kk = 0; kk < NK; ++kk) {
                 float km = 0.f, rm = 0.f;
-                for (int tt = 0; tt < NT; ++tt) { if (tt <= kk) km += mass_s[0][tt]; else rm += mass_s[0][tt]; }
+#pragma unroll
+                for (int tt = 0; tt < NT; ++tt) { if (tt <= kk) km += ms[tt]; else rm += ms[tt]; }
                 float ss = 0.f;
                 for (int c = tid; c < FD; c += 64) {
                     float kt = 0.f, rt2 = 0.f;
-                    for (int tt = 0; tt < NT; ++tt) { if (tt <= kk) kt += acc_s[0][tt][c]; else rt2 += acc_s[0][tt][c]; }
+                    for (int tt = 0; tt < NT; ++tt) { if (tt <= kk) kt += acc_s[tt * FD + c]; else rt2 += acc_s[tt * FD + c]; }
                     const float oS = kt / km;
                     if (a.o_s) a.o_s[((int64_t)a.ks.perm[kk] * R + r) * FD + c] = oS;
                     if (rm > 0.f) { const float df = rt2 / rm - oS; ss = fmaf(df, df, ss); }
@@ -976,39 +1046,6 @@ fused_fixup_kernel(FusedArgs a, int32_t *topk_idx) {
                     a.dropped[(int64_t)a.ks.perm[kk] * R + r] = rm / mtot;
                 }
             }
-        }
-        if (topk_idx) {
-            int sort_len = 1;
-            while (sort_len < a.kmax) sort_len <<= 1;
-            for (int i = tid; i < sort_len; i += 256) sb[i] = 0ull;
-            __syncthreads();
-            const int64_t chunk = (n + 255) / 256;
-            const int64_t lo = tid * chunk, hi = (lo + chunk < n) ? lo + chunk : n;
-            int c = 0;
-            for (int64_t j = lo; j < hi; ++j) {
-                const uint32_t u = ord_key(z[j]);
-                c += (u > key[NK - 1]) || (u == key[NK - 1] && j <= cut[NK - 1]);
-            }
-            int total;
-            int pos = block_exclusive_scan(c, scan, &total);
-            for (int64_t j = lo; j < hi; ++j) {
-                const uint32_t u = ord_key(z[j]);
-                if ((u > key[NK - 1]) || (u == key[NK - 1] && j <= cut[NK - 1]))
-                    sb[pos++] = ((unsigned long long)u << 32) | (0xFFFFFFFFu - (uint32_t)j);
-            }
-            __syncthreads();
-            for (int size = 2; size <= sort_len; size <<= 1)
-                for (int stride = size >> 1; stride > 0; stride >>= 1) {
-                    for (int i = tid; i < sort_len / 2; i += 256) {
-                        const int lo2 = 2 * stride * (i / stride) + (i % stride), hi2 = lo2 + stride;
-                        const bool desc = (lo2 & size) == 0;
-                        const unsigned long long x = sb[lo2], y = sb[hi2];
-                        if (desc ? (x < y) : (x > y)) { sb[lo2] = y; sb[hi2] = x; }
-                    }
-                    __syncthreads();
-                }
-            for (int i = tid; i < a.kmax; i += 256)
-                topk_idx[r * a.kmax + i] = (int32_t)(0xFFFFFFFFu - (uint32_t)(sb[i] & 0xFFFFFFFFull));
         }
         __syncthreads();
     }
@@ -1101,9 +1138,9 @@ void launch_fused_finish(const FusedArgs &a, int nk, int32_t *topk_idx, hipStrea
         else hipLaunchKernelGGL((fused_sort_kernel<16, 256>), g, b, 0, st, sel, fl, a.kmax, topk_idx);
     }
     switch (nk) {
-        case 1: hipLaunchKernelGGL(fused_fixup_kernel<1>, dim3(64), dim3(256), 0, st, a, topk_idx); break;
-        case 2: hipLaunchKernelGGL(fused_fixup_kernel<2>, dim3(64), dim3(256), 0, st, a, topk_idx); break;
-        default: hipLaunchKernelGGL(fused_fixup_kernel<3>, dim3(64), dim3(256), 0, st, a, topk_idx); break;
+        case 1: hipLaunchKernelGGL(fused_fixup_kernel<1>, dim3(256), dim3(XT), 0, st, a, topk_idx); break;
+        case 2: hipLaunchKernelGGL(fused_fixup_kernel<2>, dim3(256), dim3(XT), 0, st, a, topk_idx); break;
+        default: hipLaunchKernelGGL(fused_fixup_kernel<3>, dim3(256), dim3(XT), 0, st, a, topk_idx); break;
     }
 }
 
