@@ -117,6 +117,23 @@ def test_long_rows_fp32_and_zero_iters(torch_fw):
     assert np.all(outn["n_swaps"] == 0) and np.all(outn["gap_traj"][..., 0] < 1e-6)
 
 
+@pytest.mark.parametrize("dtype,G,n,d,k", [
+    ("f32", 1, 65, 7, 64),       # one kept-key wave, element loads, one row tile
+    ("f32", 17, 301, 64, 65),    # two row tiles, two kept-key waves
+    ("f32", 33, 130, 200, 128),  # three row tiles in two groups, d past 128
+    ("bf16", 3, 700, 256, 129),  # one kept key per thread, four waves
+    ("bf16", 2, 1500, 40, 300),  # two kept keys per thread, the last wave partly filled
+    ("f32", 1, 2500, 32, 2049),  # more kept keys than the bound pass orders
+])
+def test_kept_key_and_row_tiles(torch_fw, dtype, G, n, d, k):
+    """The bound pass's kept-key layouts and the dots pass's row and column
+    tiles at their edges, against the oracle step by step."""
+    torch, fw = torch_fw
+    rows = W.sink_rows(42, n + k, 1, G, n, d, dtype, sink=4.0)
+    out = _run(torch, fw, rows, k, 4)
+    _check(rows, k, 4, out, [(0, g) for g in sorted({0, G // 2, G - 1})], method="gform", min_exact=0.5)
+
+
 def test_full_size_swap_sampled(torch_fw):
     """8 kv units x 128 rows, n = 32768, k = 1024, up to 64 swaps, in the
     benchmark's launch configuration; two rows of every unit (16 rows, one of
