@@ -2,13 +2,20 @@
 // and applies it to the group of query rows that share the head), float64.
 //
 // One workgroup per group (the rows of all query heads of a unit at one
-// position).  For each member row in turn: logits over the unit's keys,
-// softmax, the row's own top-mass set (logit desc, index asc), its weights
-// added into the group's summed mass, the dense output, and the error of its
-// own top-mass set.  Then the vote: the s keys of largest summed mass (index
-// asc on ties).  Finally each member's forced-weight error with the vote's
-// set and the vote's dropped mass, from the vote keys' logits recomputed with
-// the row's own maximum and normaliser.
+// position).  The member rows are taken RB at a time, so that every key and
+// value row read serves RB of them: logits over the unit's keys, then, each
+// row on its own NT / RB threads, softmax and the row's own top-mass set
+// (logit desc, index asc); the dense outputs of the RB rows; the error of each
+// own set.  Then the vote: the s keys of largest summed mass (index asc on
+// ties).  Finally each member's forced-weight error with the vote's set and
+// the vote's dropped mass.
+//
+// RB is the largest of 4, 2, 1 whose rows fit LDS (float64 logits, then
+// weights, of RB rows; a group of at most RB rows needs no array of summed
+// masses, and the vote keys' weights are read back instead of formed again).
+// Bound by the float64 multiply-adds and by the lanes' reductions of the
+// logits: 1536 groups of 4 rows, 4096 bf16 keys of 128 columns: 2.06 ms, 3.12 ms
+// one row at a time.
 #include "fw_internal.hpp"
 #include "instance64.hpp"
 #include "rowpass.hpp"
@@ -17,26 +24,37 @@ namespace fw {
 
 namespace {
 
-constexpr int VT = 256;  // threads per group workgroup
+constexpr int VT = 512;        // threads per group workgroup
+constexpr int kVoteList = 32;  // sets up to this size are picked by waves and merged
 
 struct VoteLds {
-    size_t xq, red, own, vote, rowsc, mu, zz, score, total;
+    size_t xq, red, own, vote, rowsc, mu, pk, zz, score, total;
 };
 
-__host__ __device__ inline VoteLds vote_lds(int64_t N, int d, int gs, int s) {
+// Layout for RB rows at a time; score only when the group has more than RB.
+__host__ __device__ inline VoteLds vote_lds(int64_t N, int d, int gs, int s, int RB) {
     VoteLds L{};
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 16); return at; };
-    L.xq = take((size_t)d * 8);
-    L.red = take((size_t)VT * 16);
-    L.own = take((size_t)s * 4);
+    L.xq = take((size_t)RB * d * 8);
+    L.red = take(4096);  // reductions; the waves' pick lists
+    L.own = take((size_t)RB * s * 4);
     L.vote = take((size_t)s * 4);
     L.rowsc = take((size_t)gs * 2 * 8);  // per member: max logit, normaliser
     L.mu = take((size_t)gs * d * 8);     // per member: dense output
-    L.zz = take((size_t)N * 8);
-    L.score = take((size_t)N * 8);
+    // masses of a set's keys per row: beside the reductions when they are few
+    L.pk = (size_t)RB * s * 8 <= 2048 ? L.red + 2048 : take((size_t)RB * s * 8);
+    L.zz = take((size_t)RB * N * 8);
+    L.score = gs > RB ? take((size_t)N * 8) : 0;
     L.total = o;
     return L;
+}
+
+// rows at a time: the most that fit, no more than the group has
+int vote_rows(int64_t N, int d, int gs, int s) {
+    for (int rb = 4; rb > 1; rb >>= 1)
+        if (rb / 2 < gs && vote_lds(N, d, gs, s, rb).total <= 160 * 1024) return rb;
+    return 1;
 }
 
 struct VoteArgs {
@@ -48,18 +66,119 @@ struct VoteArgs {
     float *es_vote, *es_top, *dropped;
 };
 
-// es(A) = ||sum_{i in A} p_i (v_i - mu)|| / p(A) for a list of keys with
-// their masses (d-dimensional sums, one column per thread).
+// Reductions and picks by teams of NW waves (threads t of the workgroup's
+// team `team`); red holds one entry per wave of the workgroup.  Every thread
+// of the workgroup calls them.
+template <typename V, typename Op>
+__device__ __forceinline__ V team_reduce(V v, V *red, int NW, Op op) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, w0 = w / NW * NW;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v = op(v, __shfl_xor(v, off));
+    __syncthreads();
+    if (lane == 0) red[w] = v;
+    __syncthreads();
+    V r = red[w0];
+    for (int i = 1; i < NW; ++i) r = op(r, red[w0 + i]);
+    return r;
+}
+
+// The s keys of largest get(j) (index asc on ties) of each team's row into
+// out[0, s); the keys t, t + NT, .. of [0, N) are thread t's of the team.
+// Up to kVoteList keys: every wave picks its own s (each pick a wave reduction
+// of the lanes' best keys; the lane that held it looks for its next), and the
+// waves' lists are merged by counting ranks.  More: s picks of the whole team.
+template <typename F>
+__device__ void team_top(F &&get, int64_t N, int s, int *out, int t, int NT, unsigned char *red) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, NW = NT >> 6, w0 = w / NW * NW;
+    double pv = INFINITY, bv = 0.0;
+    int pi = -1, bi = -1;
+    auto next = [&]() {  // this thread's best key after (pv, pi)
+        bi = -1;
+        for (int64_t j = t; j < N; j += NT) {
+            const double x = get(j);
+            const bool after = x < pv || (x == pv && (int)j > pi);
+            if (after && (bi < 0 || x > bv)) { bv = x; bi = (int)j; }
+        }
+    };
+    auto wave_best = [&](double &mv, int &mi) {
+        mv = bv;
+        mi = bi;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            const double ov = __shfl_xor(mv, off);
+            const int oi = __shfl_xor(mi, off);
+            if (top_ahead(ov, oi, mv, mi)) { mv = ov; mi = oi; }
+        }
+    };
+    next();
+    __syncthreads();
+    if (s <= kVoteList) {
+        double *cv = (double *)red;                            // [waves][s]
+        int *ci = (int *)(red + (VT / 64) * kVoteList * 8);    // [waves][s]
+        for (int u = 0; u < s; ++u) {
+            double mv;
+            int mi;
+            wave_best(mv, mi);
+            if (lane == 0) {
+                cv[w * s + u] = mv;
+                ci[w * s + u] = mi;
+            }
+            if (mi >= 0 && bi == mi) {
+                pv = mv;
+                pi = mi;
+                next();
+            }
+        }
+        __syncthreads();
+        for (int c = t; c < NW * s; c += NT) {
+            const int i = ci[w0 * s + c];
+            if (i < 0) continue;
+            const double x = cv[w0 * s + c];
+            int rank = 0;
+            for (int e = 0; e < NW * s; ++e) rank += top_ahead(cv[w0 * s + e], ci[w0 * s + e], x, i);
+            if (rank < s) out[rank] = i;
+        }
+    } else {
+        double *cv = (double *)red;
+        int *ci = (int *)(red + 512);
+        for (int u = 0; u < s; ++u) {
+            double mv;
+            int mi;
+            wave_best(mv, mi);
+            __syncthreads();
+            if (lane == 0) {
+                cv[w] = mv;
+                ci[w] = mi;
+            }
+            __syncthreads();
+            mv = cv[w0];
+            mi = ci[w0];
+            for (int i = 1; i < NW; ++i)
+                if (top_ahead(cv[w0 + i], ci[w0 + i], mv, mi)) { mv = cv[w0 + i]; mi = ci[w0 + i]; }
+            if (t == 0) out[u] = mi >= 0 ? mi : 0;  // s <= n: a key is always found
+            if (mi >= 0 && bi == mi) {
+                pv = mv;
+                pi = mi;
+                next();
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// es(A) = ||sum_{i in A} p_i (v_i - mu)|| / p(A) of each team's list of keys
+// with their masses (d-dimensional sums, one column per thread).
 template <typename T>
 __device__ double es_list(const T *vh, int d, const int *keys, const double *pk, int s, const double *mu,
-                          double *red) {
+                          double *red, int t, int NT) {
     double g2 = 0.0;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) {
+    for (int c = t; c < d; c += NT) {
         double g = 0.0;
+#pragma unroll 4
         for (int i = 0; i < s; ++i) g = fma(pk[i], (double)Elem<T>::load(vh, (int64_t)keys[i] * d + c) - mu[c], g);
         g2 = fma(g, g, g2);
     }
-    g2 = block_reduce(g2, red, OpSum());
+    g2 = team_reduce(g2, red, NT >> 6, OpSum());
     double pm = 0.0;
     for (int i = 0; i < s; ++i) pm += pk[i];
     return sqrt(g2) / pm;
@@ -67,174 +186,282 @@ __device__ double es_list(const T *vh, int d, const int *keys, const double *pk,
 
 }  // namespace
 
-template <typename T>
+template <typename T, int RB>
 __global__ void __launch_bounds__(VT) vote_group_kernel(VoteArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int tid = threadIdx.x, NT = blockDim.x;
+    constexpr int NT = VT / RB, NW = NT / 64;  // a row's team
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), team = tid / NT, t = tid % NT;
     const int64_t N = a.N;
     const int d = a.d, s = a.s, gs = a.gs;
-    const VoteLds L = vote_lds(N, d, gs, s);
+    const VoteLds L = vote_lds(N, d, gs, s, RB);
     double *xq = (double *)(smem + L.xq);
     double *redd = (double *)(smem + L.red);
-    int64_t *redi = (int64_t *)(redd + NT);
-    int *own = (int *)(smem + L.own);
     int *vote = (int *)(smem + L.vote);
     double *rowsc = (double *)(smem + L.rowsc);
     double *mus = (double *)(smem + L.mu);
     double *zz = (double *)(smem + L.zz);
     double *score = (double *)(smem + L.score);
-    double *pk = redd + NT;  // the vote keys' masses ([s] <= NT doubles, after the row loop)
+    // this thread's team's row
+    int *own = (int *)(smem + L.own) + team * s;
+    double *pk = (double *)(smem + L.pk) + team * s;
+    double *zt = zz + team * N;
+    const bool resident = gs <= RB;  // every member's weights stay in LDS
 
-    const int64_t T_ = a.G / gs;  // positions per unit
-    const int64_t bl = xcd_order(blockIdx.x, gridDim.x);  // a unit's groups on one XCD
-    const int64_t h = bl / T_, t = bl % T_;
+    const uint32_t T_ = (uint32_t)(a.G / gs);  // positions per unit
+    const uint32_t bl = (uint32_t)xcd_order(blockIdx.x, gridDim.x);  // a unit's groups on one XCD
+    const int64_t h = bl / T_, pos = bl % T_;
     const T *kh = (const T *)a.k + h * N * d;
     const T *vh = (const T *)a.v + h * N * d;
     const double scale = a.scale ? (double)a.scale[h] : (double)default_scale(d);
-    for (int64_t j = tid; j < N; j += NT) score[j] = 0.0;
+    constexpr int VEC = RowVec<T>::VEC;
+    const bool vec = d % VEC == 0;
+    const int GL = vec ? group_lanes(d, VEC) : 64, gi = lane % GL, KPW = 64 / GL, gk = lane / GL;
+    const bool has = vec && gi < d / VEC;
+    if (!resident)
+        for (int64_t j = tid; j < N; j += VT) score[j] = 0.0;
 
-    for (int m = 0; m < gs; ++m) {
-        const int64_t r = h * a.G + (int64_t)m * T_ + t;  // query head m, position t
-        const T *qr = (const T *)a.q + r * d;
-        double *mu = mus + (size_t)m * d;
-        for (int c = tid; c < d; c += NT) xq[c] = (double)Elem<T>::load(qr, c);
+    for (int m0 = 0; m0 < gs; m0 += RB) {
+        const bool mine = m0 + team < gs;  // this team has a row (absent rows work on zeros)
+        for (int e = tid; e < RB * d; e += VT) {
+            const int rr = e / d, c = e - rr * d;
+            const int64_t r = h * a.G + (int64_t)(m0 + rr) * T_ + pos;  // query head m0 + rr, position pos
+            xq[e] = m0 + rr < gs ? (double)Elem<T>::load((const T *)a.q, r * d + c) : 0.0;
+        }
         __syncthreads();
-        double xr[8];
+        // ---- logits of the RB rows -------------------------------------------------
+        auto put = [&](int64_t j, int rr, double acc) {
+            zz[rr * N + j] = scale * acc + (a.bias ? (double)a.bias[j] : 0.0);
+        };
+        if (vec) {
+            // U keys x RB rows = 16 sums per lane
+            constexpr int U = 16 / RB;
+            double xr[RB][VEC];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) xr[i] = 0.0;
-        lane_columns<T>(d, [&](int c, int slot) { xr[slot] = xq[c]; });
-        for_keys(kh, N, d, [&](int64_t j, int gi, int GL, auto &&walk) {
-            double acc = 0.0;
-            walk([&](int, int slot, float x) { acc = fma(xr[slot], (double)x, acc); });
-            acc = group_sum(acc, GL);
-            if (j >= 0 && gi == 0) zz[j] = scale * acc + (a.bias ? (double)a.bias[j] : 0.0);
-        });
-        __syncthreads();
-        double zmax = -INFINITY;
-        for (int64_t j = tid; j < N; j += NT) zmax = fmax(zmax, zz[j]);
-        zmax = block_reduce(zmax, redd, OpMax());
-        // the row's own top-mass set
-        {
-            double pv = INFINITY;
-            int64_t pi = -1;
-            for (int u = 0; u < s; ++u) {
-                double bv = 0.0;
-                int64_t bi = -1;
-                for (int64_t j = tid; j < N; j += NT) {
-                    const double z = zz[j];
-                    const bool after = z < pv || (z == pv && j > pi);
-                    if (after && (bi < 0 || z > bv || (z == bv && j < bi))) { bv = z; bi = j; }
+            for (int rr = 0; rr < RB; ++rr) {
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) xr[rr][i] = has ? xq[rr * d + gi * VEC + i] : 0.0;
+            }
+            const int64_t stride = (int64_t)(VT / 64) * KPW;
+            uint4 raw[U];
+            auto load = [&](int64_t j0) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int64_t j = j0 + u * stride + gk;
+                    raw[u] = (j < N && has) ? RowVec<T>::raw(kh + j * d, gi * VEC) : make_uint4(0u, 0u, 0u, 0u);
                 }
-                block_argmax(bv, bi, redd, redi);
-                if (tid == 0) own[u] = bi >= 0 ? (int)bi : 0;  // s <= n: a key is always found
-                pv = bv;
-                pi = bi;
+            };
+            load((int64_t)w * KPW);
+#pragma nounroll
+            for (int64_t j0 = (int64_t)w * KPW; j0 < N; j0 += stride * U) {
+                double acc[16];  // [key][row]
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float x[VEC];
+                    RowVec<T>::unpack(raw[u], x);
+#pragma unroll
+                    for (int rr = 0; rr < RB; ++rr) acc[u * RB + rr] = 0.0;
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) {
+                        const double xd = (double)x[i];
+#pragma unroll
+                        for (int rr = 0; rr < RB; ++rr) acc[u * RB + rr] = fma(xr[rr][i], xd, acc[u * RB + rr]);
+                    }
+                }
+                load(j0 + stride * U);  // in flight during the reductions
+                if (GL == 16) {
+                    // transposed: at each exchange a lane gives away half of its
+                    // sums, and lane i ends with sum i of its group
+#pragma unroll
+                    for (int half = 8; half > 0; half >>= 1) {
+                        const bool upper = (gi & half) != 0;
+#pragma unroll
+                        for (int i = 0; i < half; ++i) {
+                            const double give = upper ? acc[i] : acc[i + half];
+                            const double keep = upper ? acc[i + half] : acc[i];
+                            acc[i] = keep + __shfl_xor(give, half);
+                        }
+                    }
+                    const int64_t j = j0 + (gi / RB) * stride + gk;
+                    if (j < N) put(j, gi % RB, acc[0]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[i] = group_sum(acc[i], GL);
+                    if (gi == 0) {
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const int64_t j = j0 + u * stride + gk;
+                            if (j < N) {
+#pragma unroll
+                                for (int rr = 0; rr < RB; ++rr) put(j, rr, acc[u * RB + rr]);
+                            }
+                        }
+                    }
+                }
+            }
+        } else {
+            for (int64_t j = w; j < N; j += VT / 64) {
+                double acc[RB];
+#pragma unroll
+                for (int rr = 0; rr < RB; ++rr) acc[rr] = 0.0;
+                for (int c = lane; c < d; c += 64) {
+                    const double xd = (double)Elem<T>::load(kh, j * d + c);
+#pragma unroll
+                    for (int rr = 0; rr < RB; ++rr) acc[rr] = fma(xq[rr * d + c], xd, acc[rr]);
+                }
+#pragma unroll
+                for (int rr = 0; rr < RB; ++rr) {
+                    acc[rr] = group_sum(acc[rr], 64);
+                    if (lane == 0) put(j, rr, acc[rr]);
+                }
             }
         }
-        double lsum = 0.0;
-        for (int64_t j = tid; j < N; j += NT) lsum += exp(zz[j] - zmax);
-        lsum = block_reduce(lsum, redd, OpSum());
-        // weights in place of the logits; the group's summed mass
-        for (int64_t j = tid; j < N; j += NT) {
-            const double p = exp(zz[j] - zmax) / lsum;
-            zz[j] = p;
-            score[j] += p;
-        }
-        if (tid == 0) {
-            rowsc[2 * m] = zmax;
-            rowsc[2 * m + 1] = lsum;
-        }
         __syncthreads();
-        // dense output: each lane accumulates its columns over the keys it visits
+        // ---- each row on its team: softmax and its own top-mass set ----------------
+        double zmax = -INFINITY;
+        for (int64_t j = t; j < N; j += NT) zmax = fmax(zmax, zt[j]);
+        zmax = team_reduce(zmax, redd, NW, OpMax());
+        team_top([&](int64_t j) { return zt[j]; }, N, s, own, t, NT, smem + L.red);
+        double lsum = 0.0;
+        for (int64_t j = t; j < N; j += NT) {
+            const double e = exp(zt[j] - zmax);
+            zt[j] = e;
+            lsum += e;
+        }
+        lsum = team_reduce(lsum, redd, NW, OpSum());
+        for (int64_t j = t; j < N; j += NT) zt[j] = zt[j] / lsum;
+        if (t == 0 && mine) {
+            rowsc[2 * (m0 + team)] = zmax;
+            rowsc[2 * (m0 + team) + 1] = lsum;
+        }
+        for (int e = tid; e < RB * d; e += VT)
+            if (m0 + e / d < gs) mus[(size_t)m0 * d + e] = 0.0;
+        __syncthreads();
+        if (!resident)
+            for (int64_t j = tid; j < N; j += VT) {
+                double sc = score[j];
+                for (int rr = 0; rr < RB && m0 + rr < gs; ++rr) sc += zz[rr * N + j];
+                score[j] = sc;
+            }
+        // ---- dense outputs: each lane its columns over the keys it visits ----------
         {
-            constexpr int VEC = RowVec<T>::VEC;
-            double part[8];
+            double part[RB][VEC > 4 ? VEC : 4];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) part[i] = 0.0;
-            const bool vec = d % VEC == 0;
-            const int GL = vec ? group_lanes(d, VEC) : 64;
-            for_keys(vh, N, d, [&](int64_t j, int, int, auto &&walk) {
-                if (j < 0) return;
-                const double p = zz[j];
-                walk([&](int, int slot, float x) { part[slot] = fma(p, (double)x, part[slot]); });
-            });
-            for (int c = tid; c < d; c += NT) mu[c] = 0.0;
-            __syncthreads();
-            const int lane = tid & 63, gi = vec ? lane % GL : lane;
-            for (int rnd = 0; rnd < NT / 64 * (64 / GL); ++rnd) {
-                if ((tid >> 6) * (64 / GL) + lane / GL == rnd) {
-                    if (vec) {
+            for (int rr = 0; rr < RB; ++rr) {
+#pragma unroll
+                for (int i = 0; i < (VEC > 4 ? VEC : 4); ++i) part[rr][i] = 0.0;
+            }
+            if (vec) {
+                constexpr int U = 8;
+                const int64_t stride = (int64_t)(VT / 64) * KPW;
+#pragma nounroll
+                for (int64_t j0 = (int64_t)w * KPW; j0 < N; j0 += stride * U) {
+                    uint4 raw[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int64_t j = j0 + u * stride + gk;
+                        raw[u] = (j < N && has) ? RowVec<T>::raw(vh + j * d, gi * VEC) : make_uint4(0u, 0u, 0u, 0u);
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int64_t j = j0 + u * stride + gk;
+                        if (j >= N) continue;
+                        float x[VEC];
+                        RowVec<T>::unpack(raw[u], x);
+                        double pr[RB];
+#pragma unroll
+                        for (int rr = 0; rr < RB; ++rr) pr[rr] = zz[rr * N + j];
 #pragma unroll
                         for (int i = 0; i < VEC; ++i) {
-                            const int c = gi * VEC + i;
-                            if (c < d) mu[c] += part[i];
-                        }
-                    } else {
+                            const double xd = (double)x[i];
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const int c = gi + 64 * u;
-                            if (c < d) mu[c] += part[u];
+                            for (int rr = 0; rr < RB; ++rr) part[rr][i] = fma(pr[rr], xd, part[rr][i]);
+                        }
+                    }
+                }
+                // the wave's groups by a butterfly, the waves in order below
+#pragma nounroll
+                for (int off = GL; off < 64; off <<= 1) {
+#pragma unroll
+                    for (int rr = 0; rr < RB; ++rr) {
+#pragma unroll
+                        for (int i = 0; i < VEC; ++i) part[rr][i] += __shfl_xor(part[rr][i], off);
+                    }
+                }
+            } else {
+                for (int64_t j = w; j < N; j += VT / 64) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int c = lane + 64 * i;
+                        const double xd = c < d ? (double)Elem<T>::load(vh, j * d + c) : 0.0;
+#pragma unroll
+                        for (int rr = 0; rr < RB; ++rr) part[rr][i] = fma(zz[rr * N + j], xd, part[rr][i]);
+                    }
+                }
+            }
+#pragma nounroll
+            for (int x = 0; x < VT / 64; ++x) {
+                if (w == x && (vec ? has && gk == 0 : true)) {
+#pragma unroll
+                    for (int rr = 0; rr < RB; ++rr) {
+                        if (m0 + rr >= gs) continue;
+                        double *mu = mus + (size_t)(m0 + rr) * d;
+#pragma unroll
+                        for (int i = 0; i < (VEC > 4 ? VEC : 4); ++i) {
+                            const int c = vec ? gi * VEC + i : lane + 64 * i;
+                            if (c < d && (!vec || i < VEC)) mu[c] += part[rr][i];
                         }
                     }
                 }
                 __syncthreads();
             }
         }
-        // the row's own top-mass error (keys with their weights, ascending order
-        // is not needed: the sums run over the list)
-        {
-            double *pown = redd + NT;  // masses of the own keys ([s] <= NT doubles)
-            for (int u = tid; u < s; u += NT) pown[u] = zz[own[u]];
-            __syncthreads();
-            const double es = es_list<T>(vh, d, own, pown, s, mu, redd);
-            if (tid == 0) a.es_top[r] = (float)(s >= N ? 0.0 : es);
-        }
-        __syncthreads();  // zz, own and pown are reused by the next member
+        // ---- each row's own top-mass error ------------------------------------------
+        for (int u = t; u < s; u += NT) pk[u] = zt[own[u]];
+        __syncthreads();
+        const double es = es_list<T>(vh, d, own, pk, s, mus + (size_t)(mine ? m0 + team : 0) * d, redd, t, NT);
+        if (t == 0 && mine) a.es_top[h * a.G + (int64_t)(m0 + team) * T_ + pos] = (float)(s >= N ? 0.0 : es);
+        __syncthreads();
     }
 
     // ---- the vote: s keys of largest summed mass, index asc on ties ---------------
-    {
-        double pv = INFINITY;
-        int64_t pi = -1;
-        for (int u = 0; u < s; ++u) {
-            double bv = 0.0;
-            int64_t bi = -1;
-            for (int64_t j = tid; j < N; j += NT) {
-                const double x = score[j];
-                const bool after = x < pv || (x == pv && j > pi);
-                if (after && (bi < 0 || x > bv || (x == bv && j < bi))) { bv = x; bi = j; }
-            }
-            block_argmax(bv, bi, redd, redi);
-            if (tid == 0) {
-                vote[u] = bi >= 0 ? (int)bi : 0;
-                a.vote_idx[(h * T_ + t) * s + u] = vote[u];
-            }
-            pv = bv;
-            pi = bi;
-        }
-    }
-    __syncthreads();
+    team_top(
+        [&](int64_t j) {
+            if (!resident) return score[j];
+            double sc = 0.0;
+#pragma unroll
+            for (int rr = 0; rr < RB; ++rr)
+                if (rr < gs) sc += zz[rr * N + j];
+            return sc;
+        },
+        N, s, vote, tid, VT, smem + L.red);
+    for (int u = tid; u < s; u += VT) a.vote_idx[(h * T_ + pos) * s + u] = vote[u];
 
     // ---- each member under the vote's set -------------------------------------------
-    for (int m = 0; m < gs; ++m) {
-        const int64_t r = h * a.G + (int64_t)m * T_ + t;
-        const T *qr = (const T *)a.q + r * d;
-        const double zmax = rowsc[2 * m], lsum = rowsc[2 * m + 1];
-        for (int c = tid; c < d; c += NT) xq[c] = (double)Elem<T>::load(qr, c);
-        __syncthreads();
-        // the vote keys' weights for this row, from their logits recomputed in
-        // float64 (summed in column order: rounding-level differences from the
-        // row pass's grouped sums) with the row's own maximum and normaliser
-        for (int u = tid; u < s; u += NT) {
-            const int j = vote[u];
-            double acc = 0.0;
-            for (int c = 0; c < d; ++c) acc = fma(xq[c], (double)Elem<T>::load(kh, (int64_t)j * d + c), acc);
-            const double z = scale * acc + (a.bias ? (double)a.bias[j] : 0.0);
-            pk[u] = exp(z - zmax) / lsum;
+    for (int m0 = 0; m0 < gs; m0 += RB) {
+        const bool mine = m0 + team < gs;
+        const int m = mine ? m0 + team : 0;
+        const int64_t r = h * a.G + (int64_t)m * T_ + pos;
+        if (resident) {
+            for (int u = t; u < s; u += NT) pk[u] = zt[vote[u]];
+        } else {
+            // the weights again, from the vote keys' logits (summed in column order:
+            // rounding-level differences from the row pass's grouped sums) with the
+            // row's own maximum and normaliser
+            const double zmax = rowsc[2 * m], lsum = rowsc[2 * m + 1];
+            const T *qr = (const T *)a.q + r * d;
+            for (int u = t; u < s; u += NT) {
+                const int j = vote[u];
+                double acc = 0.0;
+#pragma unroll 8
+                for (int c = 0; c < d; ++c)
+                    acc = fma((double)Elem<T>::load(qr, c), (double)Elem<T>::load(kh, (int64_t)j * d + c), acc);
+                const double z = scale * acc + (a.bias ? (double)a.bias[j] : 0.0);
+                pk[u] = exp(z - zmax) / lsum;
+            }
         }
         __syncthreads();
-        const double es = es_list<T>(vh, d, vote, pk, s, mus + (size_t)m * d, redd);
-        if (tid == 0) {
+        const double es = es_list<T>(vh, d, vote, pk, s, mus + (size_t)m * d, redd, t, NT);
+        if (t == 0 && mine) {
             double pv = 0.0;
             for (int u = 0; u < s; ++u) pv += pk[u];
             a.es_vote[r] = (float)(s >= N ? 0.0 : es);
@@ -246,8 +473,10 @@ __global__ void __launch_bounds__(VT) vote_group_kernel(VoteArgs a) {
 
 // ---------------------------------------------------------------------------
 bool vote_supported(const fw_rows &rows, int s, int gs) {
-    if (gs < 1 || rows.G % gs != 0 || s < 1 || s > rows.n || s > VT) return false;
-    return vote_lds(rows.n, (int)rows.d, gs, s).total <= 160 * 1024;
+    if (gs < 1 || rows.G % gs != 0 || s < 1 || s > rows.n || s > 256) return false;
+    // one row at a time with the summed masses beside it
+    const size_t score = gs > 1 ? 0 : (size_t)rows.n * 8;
+    return vote_lds(rows.n, (int)rows.d, gs, s, 1).total + score <= 160 * 1024;
 }
 
 hipError_t launch_vote(const fw_rows &rows, int s, int gs, int32_t *vote_idx, float *es_vote, float *es_top,
@@ -269,12 +498,21 @@ hipError_t launch_vote(const fw_rows &rows, int s, int gs, int32_t *vote_idx, fl
     a.es_vote = es_vote;
     a.es_top = es_top;
     a.dropped = dropped;
-    const size_t lds = vote_lds(rows.n, (int)rows.d, gs, s).total;
-    const unsigned groups = (unsigned)(rows.H * (rows.G / gs));
-    if (rows.dtype == FW_BF16)
-        hipLaunchKernelGGL(vote_group_kernel<uint16_t>, dim3(groups), dim3(VT), lds, st, a);
-    else
-        hipLaunchKernelGGL(vote_group_kernel<float>, dim3(groups), dim3(VT), lds, st, a);
+    const int rb = vote_rows(rows.n, (int)rows.d, gs, s);
+    const size_t lds = vote_lds(rows.n, (int)rows.d, gs, s, rb).total;
+    const dim3 g((unsigned)(rows.H * (rows.G / gs)));
+#define FW_VOTE(T)                                                                                        \
+    switch (rb) {                                                                                         \
+        case 4: hipLaunchKernelGGL((vote_group_kernel<T, 4>), g, dim3(VT), lds, st, a); break;            \
+        case 2: hipLaunchKernelGGL((vote_group_kernel<T, 2>), g, dim3(VT), lds, st, a); break;            \
+        default: hipLaunchKernelGGL((vote_group_kernel<T, 1>), g, dim3(VT), lds, st, a); break;           \
+    }
+    if (rows.dtype == FW_BF16) {
+        FW_VOTE(uint16_t)
+    } else {
+        FW_VOTE(float)
+    }
+#undef FW_VOTE
     return hipGetLastError();
 }
 

@@ -83,7 +83,12 @@ def test_group_of_one_votes_its_own_top_mass_set(torch_fw):
     (2, 6, 40, 16, 4, 3, 2.0, 0.0),    # vector loads
     (2, 8, 37, 12, 6, 4, 3.0, 4.0),    # ragged n, one element per lane
     (3, 4, 64, 64, 8, 2, 1.5, 4.0),
-    (2, 4, 300, 16, 80, 2, 1.0, 0.0),  # s > 64: one workgroup argmax per pick
+    (2, 4, 300, 16, 80, 2, 1.0, 0.0),  # s > 32: one team argmax per pick
+    (1, 6, 70, 64, 32, 6, 1.5, 0.0),   # six rows four at a time: summed masses, weights formed again; 16 lanes per key
+    (1, 3, 65, 128, 33, 3, 1.5, 4.0),  # a team without a row; 32 lanes per key
+    (1, 2, 7000, 20, 9, 2, 1.0, 0.0),  # rows too long for four at a time
+    (1, 5, 7000, 21, 4, 5, 1.0, 0.0),  # one at a time, one element per lane
+    (2, 1, 5, 7, 5, 1, 1.0, 0.0),      # every key kept, fewer keys than threads
 ])
 def test_small_groups_fp32(torch_fw, cfg):
     torch, fw = torch_fw
