@@ -4,7 +4,7 @@
 // One threshold tau over every unit's non-floor scores: the quota = budget -
 // H*floor largest entries in the order (score desc, unit asc, position asc)
 // are kept, plus each unit's last `floor` positions.  tau is found by a
-// device-wide radix select (four 8-bit passes over order-preserving keys);
+// device-wide radix select (digits of 11, 11 and 10 bits of order-preserving keys);
 // entries equal to tau are taken in (unit, position) order.  Kept rows are
 // then gathered unit after unit, positions ascending, as bit copies.
 //
@@ -17,10 +17,12 @@
 namespace fw {
 
 namespace {
+constexpr int kSelDigit = 2048;  // bins of a radix pass
+
 struct SelState {
     uint32_t prefix, pmask;
     int64_t rem;
-    uint32_t hist[256];
+    uint32_t hist[kSelDigit];
 };
 
 struct CompactLayout {
@@ -64,15 +66,44 @@ __device__ __forceinline__ bool offered(const uint32_t *ckey, const int64_t *ccu
 // Per unit (one workgroup): its capnf-th best non-floor key (capnf < nf) by a
 // radix select over order keys, then the position cut among equal keys
 // (ascending positions).  capnf = 0 offers no key.
-__global__ void __launch_bounds__(256)
+constexpr int kUnitThreads = 1024;  // one workgroup per unit: enough waves for the unit's reads
+
+// One wave: the bin of hist (256 bins, from the top) that holds the rem-th
+// entry, and the entries above it.
+__device__ __forceinline__ void wave_pick(const uint32_t *hist, int64_t rem, uint32_t *bin, int64_t *above) {
+    const int lane = threadIdx.x & 63;
+    int64_t c[4], sum = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        c[i] = hist[255 - (4 * lane + i)];
+        sum += c[i];
+    }
+    int64_t inc = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int64_t o = __shfl_up(inc, off);
+        if (lane >= off) inc += o;
+    }
+    int64_t before = inc - sum;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        if (before < rem && rem <= before + c[i]) {
+            *bin = 255 - (4 * lane + i);
+            *above = before;
+        }
+        before += c[i];
+    }
+}
+
+__global__ void __launch_bounds__(kUnitThreads)
 unit_cap_kernel(const float *__restrict__ imp, int64_t n, int64_t nf, int64_t capnf, uint32_t *ckey,
                 int64_t *ccut) {
     __shared__ uint32_t hist[256];
-    __shared__ uint32_t s_prefix, s_mask;
-    __shared__ int64_t s_rem;
-    __shared__ int scan[256];
+    __shared__ uint32_t s_bin;
+    __shared__ int64_t s_above;
+    __shared__ int scan[kUnitThreads];
     const int64_t h = blockIdx.x;
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, NT = blockDim.x;
     const float *r = imp + h * n;
     if (capnf == 0) {
         if (t == 0) {
@@ -81,37 +112,24 @@ unit_cap_kernel(const float *__restrict__ imp, int64_t n, int64_t nf, int64_t ca
         }
         return;
     }
-    if (t == 0) {
-        s_prefix = 0;
-        s_mask = 0;
-        s_rem = capnf;
-    }
+    uint32_t key = 0, mask = 0;
+    int64_t need = capnf;
     for (int shift = 24; shift >= 0; shift -= 8) {
-        hist[t] = 0;
+        if (t < 256) hist[t] = 0;
         __syncthreads();
-        const uint32_t prefix = s_prefix, mask = s_mask;
-        for (int64_t j = t; j < nf; j += 256) {
+        for (int64_t j = t; j < nf; j += NT) {
             const uint32_t u = ord_key(r[j]);
-            if ((u & mask) == prefix) atomicAdd(&hist[(u >> shift) & 255u], 1u);
+            if ((u & mask) == key) atomicAdd(&hist[(u >> shift) & 255u], 1u);
         }
         __syncthreads();
-        if (t == 0) {
-            int64_t cum = 0;
-            int b = 0;
-            for (int bb = 255; bb >= 0; --bb) {
-                if (cum + (int64_t)hist[bb] >= s_rem) { b = bb; break; }
-                cum += hist[bb];
-            }
-            s_prefix |= (uint32_t)b << shift;
-            s_mask |= 255u << shift;
-            s_rem -= cum;
-        }
+        if (t < 64) wave_pick(hist, need, &s_bin, &s_above);
         __syncthreads();
+        key |= s_bin << shift;
+        mask |= 255u << shift;
+        need -= s_above;
     }
-    // the s_rem-th key equal to the cut key, positions ascending
-    const uint32_t key = s_prefix;
-    const int64_t need = s_rem;
-    const int64_t chunk = (nf + 255) / 256;
+    // the need-th key equal to the cut key, positions ascending
+    const int64_t chunk = (nf + NT - 1) / NT;
     const int64_t lo = t * chunk, hi = (lo + chunk < nf) ? lo + chunk : nf;
     int c = 0;
     for (int64_t j = lo; j < hi; ++j) c += ord_key(r[j]) == key;
@@ -143,101 +161,56 @@ maxpool_kernel(const float *__restrict__ r, int64_t H, int64_t n, int half, floa
 }
 
 __global__ void sel_init_kernel(SelState *s, int64_t quota) {
-    const int t = threadIdx.x;
-    if (t < 256) s->hist[t] = 0;
-    if (t == 0) {
+    for (int t = threadIdx.x; t < kSelDigit; t += blockDim.x) s->hist[t] = 0;
+    if (threadIdx.x == 0) {
         s->prefix = 0;
         s->pmask = 0;
         s->rem = quota;
     }
 }
 
-// histogram of the next 8-bit digit over non-floor entries matching the prefix.
+// histogram of the next digit over non-floor entries matching the prefix.
 // Block b reads slice b / H of unit b % H (the grid is a multiple of H), so
-// positions come without a division per entry; each wave counts into its own
-// copy of the bins (fewer lanes contend for one LDS word), summed at the end.
+// positions come without a division per entry, four scores per load where the
+// rows allow it.  Bound by the scores' read: 33.6 M scores,
+// three passes of 54 us (four of 80 us with 8-bit digits and one score per load).
 __global__ void __launch_bounds__(256)
-sel_hist_kernel(const float *__restrict__ imp, int64_t H, int64_t n, int64_t nf, int shift,
+sel_hist_kernel(const float *__restrict__ imp, int64_t H, int64_t n, int64_t nf, int shift, uint32_t dmask,
                 SelState *s, const uint32_t *ckey, const int64_t *ccut) {
-    __shared__ uint32_t hw[4][256];
-    const int t = threadIdx.x, w = t >> 6;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) hw[i][t] = 0;
+    __shared__ uint32_t hw[2][kSelDigit];  // one copy of the bins per two waves
+    const int t = threadIdx.x;
+    for (int i = t; i < 2 * kSelDigit; i += 256) hw[0][i] = 0;
     __syncthreads();
+    uint32_t *mine = hw[t >> 7];
     const uint32_t prefix = s->prefix, pmask = s->pmask;
     const int64_t hh = blockIdx.x % H;
     const int64_t nsl = gridDim.x / H, sl = blockIdx.x / H;
     const float *row = imp + hh * n;
-    for (int64_t j = sl * 256 + t; j < nf; j += nsl * 256) {
-        const uint32_t u = ord_key(row[j]);
-        if ((u & pmask) == prefix && offered(ckey, ccut, hh, j, u)) atomicAdd(&hw[w][(u >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    const uint32_t c = hw[0][t] + hw[1][t] + hw[2][t] + hw[3][t];
-    if (c) atomicAdd(&s->hist[t], c);
-}
-
-// choose the digit holding the rem-th largest; clear the histogram
-__global__ void sel_pick_kernel(SelState *s, int shift) {
-    if (threadIdx.x == 0) {
-        int64_t cum = 0;
-        int b = 0;
-        for (int bb = 255; bb >= 0; --bb) {
-            if (cum + (int64_t)s->hist[bb] >= s->rem) { b = bb; break; }
-            cum += s->hist[bb];
-        }
-        s->prefix |= (uint32_t)b << shift;
-        s->pmask |= 255u << shift;
-        s->rem -= cum;
-    }
-    __syncthreads();
-    if (threadIdx.x < 256) s->hist[threadIdx.x] = 0;
-}
-
-// per unit: entries above tau and equal to tau among the non-floor positions
-// (16-byte loads of four scores where the row allows them)
-__global__ void __launch_bounds__(256)
-unit_counts_kernel(const float *__restrict__ imp, int64_t n, int64_t nf, const SelState *s,
-                   int64_t quota, int64_t *cgt, int64_t *ceq, const uint32_t *ckey, const int64_t *ccut) {
-    __shared__ int64_t r1[256], r2[256];
-    const int64_t h = blockIdx.x;
-    const int t = threadIdx.x;
-    const uint32_t key = s->prefix;
-    const float *row = imp + h * n;
-    int64_t a = 0, b = 0;
     auto one = [&](int64_t j, float x) {
         const uint32_t u = ord_key(x);
-        const bool o = offered(ckey, ccut, h, j, u);
-        a += o && (u > key);
-        b += o && (u == key);
+        if ((u & pmask) == prefix && offered(ckey, ccut, hh, j, u)) atomicAdd(&mine[(u >> shift) & dmask], 1u);
     };
-    if (quota > 0) {
-        int64_t j0 = 0;
-        if ((n & 3) == 0) {
-            const int64_t nv = nf / 4;   // whole groups of four non-floor positions
-            for (int64_t g = t; g < nv; g += 256) {
-                const float4 y = *(const float4 *)(row + 4 * g);
-                one(4 * g, y.x);
-                one(4 * g + 1, y.y);
-                one(4 * g + 2, y.z);
-                one(4 * g + 3, y.w);
-            }
-            j0 = 4 * nv;
+    int64_t j0 = 0;
+    if ((n & 3) == 0) {
+        const int64_t nv = nf / 4;  // whole groups of four non-floor positions
+#pragma unroll 4
+        for (int64_t g = sl * 256 + t; g < nv; g += nsl * 256) {
+            const float4 y = *(const float4 *)(row + 4 * g);
+            one(4 * g, y.x);
+            one(4 * g + 1, y.y);
+            one(4 * g + 2, y.z);
+            one(4 * g + 3, y.w);
         }
-        for (int64_t j = j0 + t; j < nf; j += 256) one(j, row[j]);
+        j0 = 4 * nv;
     }
-    a = block_reduce(a, r1, OpSum());
-    b = block_reduce(b, r2, OpSum());
-    if (t == 0) {
-        cgt[h] = a;
-        ceq[h] = b;
+    for (int64_t j = j0 + sl * 256 + t; j < nf; j += nsl * 256) one(j, row[j]);
+    __syncthreads();
+    for (int i = t; i < kSelDigit; i += 256) {
+        const uint32_t c = hw[0][i] + hw[1][i];
+        if (c) atomicAdd(&s->hist[i], c);
     }
 }
 
-// ties taken per unit, offsets, tau and the bytes held (one workgroup).  The
-// units take the remaining ties in unit order: unit h takes
-// clamp(rem - (ties of the units before it), 0, its ties), so both the ties
-// taken and the offsets are prefix sums, formed 256 units at a time.
 __device__ __forceinline__ int64_t block_excl_scan64(int64_t v, int64_t *buf, int64_t *total) {
     const int t = threadIdx.x, nt = blockDim.x;
     buf[t] = v;
@@ -254,6 +227,78 @@ __device__ __forceinline__ int64_t block_excl_scan64(int64_t v, int64_t *buf, in
     return incl - v;
 }
 
+// choose the digit holding the rem-th largest; clear the histogram
+__global__ void __launch_bounds__(256) sel_pick_kernel(SelState *s, int shift, uint32_t dmask) {
+    constexpr int PB = kSelDigit / 256;
+    __shared__ int64_t buf[256];
+    const int t = threadIdx.x;
+    const int64_t rem = s->rem;
+    int64_t c[PB], sum = 0;
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {  // from the top
+        c[i] = s->hist[kSelDigit - 1 - (t * PB + i)];
+        sum += c[i];
+    }
+    int64_t total;
+    int64_t before = block_excl_scan64(sum, buf, &total);
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {
+        if (before < rem && rem <= before + c[i]) {
+            s->prefix |= (uint32_t)(kSelDigit - 1 - (t * PB + i)) << shift;
+            s->pmask |= dmask << shift;
+            s->rem = rem - before;
+        }
+        before += c[i];
+    }
+#pragma unroll
+    for (int i = 0; i < PB; ++i) s->hist[kSelDigit - 1 - (t * PB + i)] = 0;
+}
+
+// per unit: entries above tau and equal to tau among the non-floor positions
+// (16-byte loads of four scores where the row allows them)
+__global__ void __launch_bounds__(kUnitThreads)
+unit_counts_kernel(const float *__restrict__ imp, int64_t n, int64_t nf, const SelState *s,
+                   int64_t quota, int64_t *cgt, int64_t *ceq, const uint32_t *ckey, const int64_t *ccut) {
+    __shared__ int64_t r1[kUnitThreads / 64], r2[kUnitThreads / 64];
+    const int64_t h = blockIdx.x;
+    const int t = threadIdx.x, NT = blockDim.x;
+    const uint32_t key = s->prefix;
+    const float *row = imp + h * n;
+    int64_t a = 0, b = 0;
+    auto one = [&](int64_t j, float x) {
+        const uint32_t u = ord_key(x);
+        const bool o = offered(ckey, ccut, h, j, u);
+        a += o && (u > key);
+        b += o && (u == key);
+    };
+    if (quota > 0) {
+        int64_t j0 = 0;
+        if ((n & 3) == 0) {
+            const int64_t nv = nf / 4;   // whole groups of four non-floor positions
+#pragma unroll 4
+            for (int64_t g = t; g < nv; g += NT) {
+                const float4 y = *(const float4 *)(row + 4 * g);
+                one(4 * g, y.x);
+                one(4 * g + 1, y.y);
+                one(4 * g + 2, y.z);
+                one(4 * g + 3, y.w);
+            }
+            j0 = 4 * nv;
+        }
+        for (int64_t j = j0 + t; j < nf; j += NT) one(j, row[j]);
+    }
+    a = block_reduce(a, r1, OpSum());
+    b = block_reduce(b, r2, OpSum());
+    if (t == 0) {
+        cgt[h] = a;
+        ceq[h] = b;
+    }
+}
+
+// ties taken per unit, offsets, tau and the bytes held (one workgroup).  The
+// units take the remaining ties in unit order: unit h takes
+// clamp(rem - (ties of the units before it), 0, its ties), so both the ties
+// taken and the offsets are prefix sums, formed 256 units at a time.
 __global__ void __launch_bounds__(256)
 unit_offsets_kernel(int64_t H, int64_t hpl, int64_t n, int64_t f, int64_t quota, const SelState *s,
                     const int64_t *cgt, const int64_t *ceq, int64_t *take, int64_t *offsets,
@@ -310,8 +355,8 @@ unit_offsets_kernel(int64_t H, int64_t hpl, int64_t n, int64_t f, int64_t quota,
 // scores are read in tiles of 16 consecutive positions per thread (16-byte
 // loads: a wave reads whole lines), and one scan per tile places them.  Each
 // thread's count of plain keeps (floor, or offered above the threshold key)
-// and of offered keys equal to it share one word (16 bits each: a tile holds
-// 4096 positions), and ties are kept in position order while the unit's
+// and of offered keys equal to it share one word (16 bits each: a tile holds at
+// most 16,384 positions), and ties are kept in position order while the unit's
 // quota of them lasts, so the number of ties kept before a thread follows
 // from the ties before it.
 __device__ __forceinline__ int keep_block_scan(int v, int *wsum, int *total) {
@@ -335,13 +380,13 @@ __device__ __forceinline__ int keep_block_scan(int v, int *wsum, int *total) {
     return before + x - v;
 }
 
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kUnitThreads)
 unit_keep_kernel(const float *__restrict__ imp, int64_t n, int64_t f, int64_t quota,
                  const SelState *s, const int64_t *take, const int64_t *offsets, int32_t *kept_pos,
                  float *dropped, const uint32_t *ckey, const int64_t *ccut) {
     constexpr int PER = 16;
-    __shared__ int wsum[4];
-    __shared__ double red[256];
+    __shared__ int wsum[kUnitThreads / 64];
+    __shared__ double red[kUnitThreads / 64];
     const int64_t h = blockIdx.x;
     const int t = threadIdx.x;
     const uint32_t key = s->prefix;
@@ -352,7 +397,7 @@ unit_keep_kernel(const float *__restrict__ imp, int64_t n, int64_t f, int64_t qu
     int64_t out = offsets[h];
     int64_t eq_run = 0;   // offered keys equal to the threshold key before this tile
     double dm = 0.0;
-    for (int64_t base = 0; base < n; base += (int64_t)PER * 256) {
+    for (int64_t base = 0; base < n; base += (int64_t)PER * blockDim.x) {
         const int64_t j0 = base + (int64_t)PER * t;
         float x[PER];
         if (vec && j0 + PER <= n) {
@@ -464,8 +509,11 @@ hipError_t launch_compact(int dtype, const void *k, const void *v, int64_t H, in
     // the per-unit candidate cut, when a cap leaves some non-floor key out
     const uint32_t *ckey = nullptr;
     const int64_t *ccut = nullptr;
+    // 16 waves per unit for long units (256 units of 131,072 scores: counts 25 us,
+    // positions 58 us; 66 and 129 with four waves)
+    const unsigned ut = n > 8192 ? kUnitThreads : 256;
     if (cap > 0 && cap - f < nf) {
-        hipLaunchKernelGGL(unit_cap_kernel, dim3((unsigned)H), dim3(256), 0, st, importance, n, nf, cap - f, L.ckey,
+        hipLaunchKernelGGL(unit_cap_kernel, dim3((unsigned)H), dim3(ut), 0, st, importance, n, nf, cap - f, L.ckey,
                            L.ccut);
         ckey = L.ckey;
         ccut = L.ccut;
@@ -474,23 +522,26 @@ hipError_t launch_compact(int dtype, const void *k, const void *v, int64_t H, in
     const int64_t row_bytes = d * elem;
     hipLaunchKernelGGL(sel_init_kernel, dim3(1), dim3(256), 0, st, L.sel, quota);
     if (quota > 0) {
-        // slices per unit so that the grid holds about 4096 blocks (a multiple of H)
-        const int64_t per = (nf + 255) / 256;
-        int64_t nsl = 4096 / H;
+        // slices per unit so that the grid holds about 2048 blocks (a multiple of
+        // H), each of at least 4096 scores: a block adds up to 2048 bins at its end
+        const int64_t per = (nf + 4095) / 4096;
+        int64_t nsl = 2048 / H;
         if (nsl > per) nsl = per;
         if (nsl < 1) nsl = 1;
         const unsigned blocks = (unsigned)(H * nsl);
-        for (int shift = 24; shift >= 0; shift -= 8) {
-            hipLaunchKernelGGL(sel_hist_kernel, dim3(blocks), dim3(256), 0, st, importance, H, n, nf,
-                               shift, L.sel, ckey, ccut);
-            hipLaunchKernelGGL(sel_pick_kernel, dim3(1), dim3(256), 0, st, L.sel, shift);
+        for (int pass = 0; pass < 3; ++pass) {
+            const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+            const uint32_t dmask = pass < 2 ? 2047u : 1023u;
+            hipLaunchKernelGGL(sel_hist_kernel, dim3(blocks), dim3(256), 0, st, importance, H, n, nf, shift, dmask,
+                               L.sel, ckey, ccut);
+            hipLaunchKernelGGL(sel_pick_kernel, dim3(1), dim3(256), 0, st, L.sel, shift, dmask);
         }
     }
-    hipLaunchKernelGGL(unit_counts_kernel, dim3((unsigned)H), dim3(256), 0, st, importance, n, nf,
+    hipLaunchKernelGGL(unit_counts_kernel, dim3((unsigned)H), dim3(ut), 0, st, importance, n, nf,
                        L.sel, quota, L.cgt, L.ceq, ckey, ccut);
     hipLaunchKernelGGL(unit_offsets_kernel, dim3(1), dim3(256), 0, st, H, hpl, n, f, quota, L.sel,
                        L.cgt, L.ceq, L.take, offsets, tau, bytes_held, 2 * row_bytes);
-    hipLaunchKernelGGL(unit_keep_kernel, dim3((unsigned)H), dim3(256), 0, st, importance, n, f, quota,
+    hipLaunchKernelGGL(unit_keep_kernel, dim3((unsigned)H), dim3(ut), 0, st, importance, n, f, quota,
                        L.sel, L.take, offsets, kept_pos, dropped, ckey, ccut);
     if (budget > 0) {
         if (row_bytes % 16 == 0) {

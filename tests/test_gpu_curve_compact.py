@@ -139,6 +139,9 @@ def _check_compact(Knp, Vnp, imp, out, budget, floor, hpl, elem, cap=0):
     dict(H=5, hpl=5, n=200, d=16, floor=8, frac=1.0, dt="f32", ties=True, cap=30),   # every unit at its cap
     dict(H=4, hpl=2, n=64, d=8, floor=8, frac=0.5, dt="f32", ties=True, cap=8),      # cap = floor
     dict(H=4, hpl=2, n=64, d=8, floor=4, frac=0.3, dt="f32", ties=True, cap=100),    # cap above n
+    # units past 8192 positions (16 waves each), with and without whole 16-byte groups
+    dict(H=4, hpl=2, n=9001, d=8, floor=7, frac=0.2, dt="f32", ties=True, cap=2500),
+    dict(H=2, hpl=2, n=20000, d=4, floor=0, frac=0.3, dt="bf16", ties=True),
 ])
 def test_compact_exact(torch_fw, case):
     torch, fw = torch_fw
