@@ -10,6 +10,7 @@
 // the logits, weights and their window mean; (4) per unit, a stable LSD radix
 // sort of the scores (descending, ties by index); (5) a float64 suffix scan.
 #include "fw_internal.hpp"
+#include "topk_fused.hpp"
 
 namespace fw {
 
@@ -19,57 +20,140 @@ constexpr int kRowGrp = 16;   // window rows per LDS tile
 constexpr int kSortThreads = 1024;
 }  // namespace
 
-// Pass 1 (MODE 0) and pass 3 (MODE 1) share the logit computation: each
-// thread owns two keys of the chunk; window rows are processed 16 at a time.
-template <typename T, int MODE>
+// Pass 1 (MODE 0) and pass 3 (MODE 1) share the logit computation: a
+// workgroup takes kChunk keys, 16 window rows at a time; each wave a quarter of
+// the keys in tiles of 16, read as whole rows, turned through LDS and
+// multiplied on the float32 MFMA.  Its chain gives, bit for bit, the fused
+// multiply-adds over the columns in order (see scores_kernel), and the sums
+// over keys and rows below run in one fixed order, so the scores and the order
+// built on them do not depend on the tiling.  Takes every window that
+// k_window.hip does not.  64 cells of 64 rows of 8192 float32 keys of 128
+// columns: 0.42 ms a call, 1.90 ms with one thread per key reading its own row.
+template <typename T, int DC, int MODE>
 __global__ void __launch_bounds__(256)
 window_logits_kernel(const T *__restrict__ q, const T *__restrict__ k, const float *__restrict__ scale,
-                     const float *__restrict__ bias, int64_t G, int64_t n, int d, int nchunks,
+                     const float *__restrict__ bias, int64_t G, int64_t n, int d, int nchunks, int vec,
                      float *__restrict__ part_m, float *__restrict__ part_s,
                      const float *__restrict__ row_m, const float *__restrict__ row_il,
                      float *__restrict__ importance) {
-    __shared__ float Qs[kRowGrp][257];
-    __shared__ float zt[kRowGrp][kChunk + 1];
+    constexpr bool B16 = sizeof(T) == 2;
+    constexpr int E = 16 / (int)sizeof(T);  // elements per 16-byte chunk
+    constexpr int CH = DC * 32 / E;         // chunks per row
+    constexpr int LD = CH / 4;              // loads per lane and tile (16 rows x CH chunks / 64)
+    constexpr int RS = CH + 4;              // words per row and kg: no bank conflicts on the reads
+    extern __shared__ __align__(16) uint32_t lds_w[];  // [wave][kg][row][chunk]
+    __shared__ float zt[MODE == 0 ? kRowGrp : 1][kChunk + 1];  // logits; MODE 1: the keys' sums
     __shared__ float red[256];
-    const int tid = threadIdx.x;
-    const int64_t h = blockIdx.x / nchunks;
-    const int ch = blockIdx.x % nchunks;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int m16 = lane & 15, kg = lane >> 4;
+    uint32_t *tile = lds_w + w * (64 * RS);
+    const uint4 *mine = (const uint4 *)(tile + (kg * 16 + m16) * RS);
+    const int64_t h = (uint32_t)blockIdx.x / (uint32_t)nchunks;
+    const int ch = (uint32_t)blockIdx.x % (uint32_t)nchunks;
     const int64_t j0 = (int64_t)ch * kChunk;
     const T *qh = q + h * G * d;
     const T *kh = k + h * n * d;
     const float sc = scale ? scale[h] : (float)(1.0 / sqrt((double)d));
-    float racc[2] = {0.f, 0.f};
+    uint4 raw[LD];
+    auto load = [&](const T *base, int64_t row0, int64_t rows) {
+#pragma unroll
+        for (int i = 0; i < LD; ++i) {
+            const int id = lane + 64 * i, c = (id % CH) * E;
+            const int64_t j = row0 + id / CH;
+            raw[i] = make_uint4(0u, 0u, 0u, 0u);
+            if (j >= rows || c >= d) continue;
+            if (vec) {
+                raw[i] = *(const uint4 *)(base + j * d + c);
+            } else {
+                T x[E];
+#pragma unroll
+                for (int e = 0; e < E; ++e) x[e] = c + e < d ? base[j * d + c + e] : (T)0;
+                raw[i] = __builtin_bit_cast(uint4, x);
+            }
+        }
+    };
+    auto stage = [&]() {  // raw to LDS; this wave's reads of it follow
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < LD; ++i) {
+            const int id = lane + 64 * i;
+            uint32_t *to = tile + (id / CH) * RS + id % CH;
+            const uint4 x = raw[i];
+            to[0] = B16 ? __builtin_amdgcn_perm(x.z, x.x, 0x05040100u) : x.x;
+            to[16 * RS] = B16 ? __builtin_amdgcn_perm(x.z, x.x, 0x07060302u) : x.y;
+            to[32 * RS] = B16 ? __builtin_amdgcn_perm(x.w, x.y, 0x05040100u) : x.z;
+            to[48 * RS] = B16 ? __builtin_amdgcn_perm(x.w, x.y, 0x07060302u) : x.w;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    if (MODE == 1)
+        for (int e = tid; e < kChunk; e += 256) zt[0][e] = 0.f;
+    __syncthreads();
     for (int64_t g0 = 0; g0 < G; g0 += kRowGrp) {
         const int gn = (G - g0 < kRowGrp) ? (int)(G - g0) : kRowGrp;
-        for (int e = tid; e < kRowGrp * d; e += 256) {
-            const int rr = e / d, cc = e % d;
-            Qs[rr][cc] = (rr < gn) ? Elem<T>::load(qh, (g0 + rr) * d + cc) : 0.f;
+        uint4 qf[LD];
+        load(qh, g0, G);
+        stage();
+#pragma unroll
+        for (int f = 0; f < LD; ++f) qf[f] = mine[f];
+        // lane: key m16 of a tile, window rows 4 kg .. 4 kg + 3 of the group
+        float rm[4], ril[4];
+        if (MODE == 1) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const bool ok = 4 * kg + i < gn;
+                rm[i] = ok ? row_m[h * G + g0 + 4 * kg + i] : 0.f;
+                ril[i] = ok ? row_il[h * G + g0 + 4 * kg + i] : 0.f;
+            }
         }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int jl = tid + 256 * u;
+        constexpr int KT = kChunk / 64;  // key tiles per wave
+        load(kh, j0 + w * (kChunk / 4), n);
+        for (int t = 0; t < KT; ++t) {
+            const int jl = w * (kChunk / 4) + 16 * t + m16;
             const int64_t j = j0 + jl;
-            float acc[kRowGrp];
+            stage();
+            if (t + 1 < KT) load(kh, j0 + w * (kChunk / 4) + 16 * (t + 1), n);
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int g = 0; g < kRowGrp; ++g) acc[g] = 0.f;
-            if (j < n) {
-                for (int c = 0; c < d; ++c) {
-                    const float kv = Elem<T>::load(kh, j * d + c);
+            for (int f = 0; f < LD; ++f) {
+                const uint4 kf = mine[f];
+                const uint32_t kw[4] = {kf.x, kf.y, kf.z, kf.w}, qw[4] = {qf[f].x, qf[f].y, qf[f].z, qf[f].w};
 #pragma unroll
-                    for (int g = 0; g < kRowGrp; ++g) acc[g] = fmaf(Qs[g][c], kv, acc[g]);
+                for (int c = 0; c < 4; ++c) {
+                    if constexpr (B16) {
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(qw[c] << 16),
+                                                                   __uint_as_float(kw[c] << 16), acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(qw[c] & 0xFFFF0000u),
+                                                                   __uint_as_float(kw[c] & 0xFFFF0000u), acc, 0, 0, 0);
+                    } else {
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(qw[c]), __uint_as_float(kw[c]), acc,
+                                                                   0, 0, 0);
+                    }
                 }
             }
             const float bj = (bias && j < n) ? bias[j] : 0.f;
+            if (MODE == 0) {
 #pragma unroll
-            for (int g = 0; g < kRowGrp; ++g) {
-                const float zz = sc * acc[g] + bj;
-                if (MODE == 0) {
-                    zt[g][jl] = (j < n && g < gn) ? zz : -INFINITY;
-                } else if (j < n && g < gn) {
-                    const int64_t row = h * G + g0 + g;
-                    racc[u] += expf(zz - row_m[row]) * row_il[row];
+                for (int i = 0; i < 4; ++i) {
+                    const int g = 4 * kg + i;
+                    zt[g][jl] = (j < n && g < gn) ? fmaf(sc, acc[i], bj) : -INFINITY;
                 }
+            } else {
+                // the key's sum over the rows in order: lane group after lane group
+                float part[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) part[i] = expf(fmaf(sc, acc[i], bj) - rm[i]);
+                float r = zt[0][jl];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    float y = r;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (4 * x + i < gn) y = fmaf(part[i], ril[i], y);
+                    r = __shfl(y, 16 * x + m16);
+                }
+                if (kg == 0) zt[0][jl] = r;
             }
         }
         if (MODE == 0) {
@@ -99,11 +183,8 @@ window_logits_kernel(const T *__restrict__ q, const T *__restrict__ k, const flo
     }
     if (MODE == 1) {
         const float invG = 1.0f / (float)G;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int64_t j = j0 + tid + 256 * u;
-            if (j < n) importance[h * n + j] = racc[u] * invG;
-        }
+        for (int e = tid; e < kChunk; e += 256)
+            if (j0 + e < n) importance[h * n + j0 + e] = zt[0][e] * invG;
     }
 }
 
@@ -396,25 +477,37 @@ CurveLayout curve_layout(const fw_rows &rows, void *ws) {
 
 size_t curve_ws_bytes(const fw_rows &rows) { return curve_layout(rows, nullptr).bytes; }
 
+// both logit passes of a window that k_window.hip does not take
+template <typename T, int DC>
+static void window_general(const fw_rows &rows, const CurveLayout &L, float *importance, hipStream_t st) {
+    const int64_t H = rows.H, G = rows.G, n = rows.n;
+    const int d = (int)rows.d, nch = (int)((n + kChunk - 1) / kChunk);
+    const dim3 grid((unsigned)(H * nch));
+    const T *q = (const T *)rows.q, *k = (const T *)rows.k;
+    const int vec = d % (16 / (int)sizeof(T)) == 0 && ((uintptr_t)q | (uintptr_t)k) % 16 == 0;
+    const size_t lds = (size_t)4 * 64 * (DC * 2 * sizeof(T) + 4) * 4;
+    hipLaunchKernelGGL((window_logits_kernel<T, DC, 0>), grid, dim3(256), lds, st, q, k, rows.scale, rows.bias, G, n, d,
+                       nch, vec, L.part_m, L.part_s, nullptr, nullptr, nullptr);
+    hipLaunchKernelGGL(window_combine_kernel, dim3((unsigned)((H * G + 255) / 256)), dim3(256), 0, st, H * G, nch,
+                       L.part_m, L.part_s, L.row_m, L.row_il);
+    hipLaunchKernelGGL((window_logits_kernel<T, DC, 1>), grid, dim3(256), lds, st, q, k, rows.scale, rows.bias, G, n, d,
+                       nch, vec, nullptr, nullptr, L.row_m, L.row_il, importance);
+}
+
 template <typename T>
 static hipError_t curve_impl(const fw_rows &rows, float *importance, float *curve, int32_t *order,
                              void *ws, hipStream_t st) {
     CurveLayout L = curve_layout(rows, ws);
-    const int64_t H = rows.H, G = rows.G, n = rows.n;
-    const int d = (int)rows.d;
-    const int nch = (int)((n + kChunk - 1) / kChunk);
-    const dim3 grid((unsigned)(H * nch));
-    const T *q = (const T *)rows.q, *k = (const T *)rows.k;
+    const int64_t H = rows.H, n = rows.n;
     if (window_mfma_supported(rows)) {
         // bf16, d = 128, up to 64 window rows: MFMA scores (k_window.hip)
         launch_window_mfma(rows, L.part_m, L.part_s, L.row_m, L.row_il, importance, st);
+    } else if (rows.d <= 64) {
+        window_general<T, 2>(rows, L, importance, st);
+    } else if (rows.d <= 128) {
+        window_general<T, 4>(rows, L, importance, st);
     } else {
-        hipLaunchKernelGGL((window_logits_kernel<T, 0>), grid, dim3(256), 0, st, q, k, rows.scale,
-                           rows.bias, G, n, d, nch, L.part_m, L.part_s, nullptr, nullptr, nullptr);
-        hipLaunchKernelGGL(window_combine_kernel, dim3((unsigned)((H * G + 255) / 256)), dim3(256), 0, st,
-                           H * G, nch, L.part_m, L.part_s, L.row_m, L.row_il);
-        hipLaunchKernelGGL((window_logits_kernel<T, 1>), grid, dim3(256), 0, st, q, k, rows.scale,
-                           rows.bias, G, n, d, nch, nullptr, nullptr, L.row_m, L.row_il, importance);
+        window_general<T, 8>(rows, L, importance, st);
     }
     if (order)
         hipLaunchKernelGGL((unit_sort_kernel<true>), dim3((unsigned)H), dim3(kSortThreads), 0, st,

@@ -235,6 +235,39 @@ def test_full_size_curve_and_compact(torch_fw):
     assert worst_imp <= TOL[rows.dtype]
 
 
+@pytest.mark.parametrize("dtype,H,G,n,d,shift", [
+    ("f32", 1, 1, 1, 1, 1),
+    ("f32", 2, 17, 513, 200, 0),    # two row groups, one key past a chunk, d past 128
+    ("bf16", 2, 33, 700, 100, 1),   # element loads, unaligned operands
+    ("f32", 2, 80, 1000, 64, 0),    # five row groups
+    ("bf16", 1, 40, 511, 72, 0),    # a partial column chunk, one key short of a chunk
+])
+def test_general_window_edges(torch_fw, dtype, H, G, n, d, shift):
+    """Windows that the bf16 MFMA pass does not take, at the edges of the
+    general pass's tiles, with a masked key: importance against float64, the
+    order and the curve from the GPU's own importance."""
+    torch, fw = torch_fw
+    rows = W.window_rows(57, n + G, H, G, n, d, dtype)
+    bias = np.random.default_rng(n).standard_normal(n).astype(np.float32)
+    if n > 600:
+        bias[5] = -np.inf
+    rows.bias = bias
+    dev = fw.upload(rows)
+    for name in ("q", "k"):
+        t = dev[name]
+        dev[name] = torch.empty(t.numel() + shift, dtype=t.dtype, device="cuda")[shift:].view(t.shape).copy_(t)
+    out = fw.dropped_mass_curve(dev["q"], dev["k"], dev["scale"], dev["bias"])
+    r = t2np(out["importance"])
+    q, K = rows.as_f64("q"), rows.as_f64("k")
+    for h in range(H):
+        ref = O.importance(q[h], K[h], float(rows.scale[h]), bias.astype(np.float64))
+        # float32 logits of at most 200 products and sums of at most 80 weights
+        assert np.all(np.abs(r[h] - ref) <= 2e-5 * ref + 1e-12)
+        assert np.array_equal(t2np(out["order"])[h], np.lexsort((np.arange(n), -r[h])))
+        want = np.concatenate([np.cumsum(np.sort(r[h].astype(np.float64)))[::-1], [0.0]])
+        assert np.allclose(t2np(out["curve"])[h], want, rtol=1e-6, atol=1e-12)
+
+
 @pytest.mark.parametrize("kernel", [1, 3, 7])
 def test_maxpool_scores(torch_fw, kernel):
     """SnapKV's pooling against the oracle, bit for bit (a max of float32
