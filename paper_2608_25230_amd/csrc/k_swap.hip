@@ -20,7 +20,7 @@
 // with r_x = ||u_x||, so every pair's numerator is at least
 //     A_i + B_j - 2 r_i r_j,   A_i = ||g - u_i||^2,  B_j = ||u_j||^2 + 2 g.u_j,
 // and its denominator is (P - p_i + p_j)^2.  An upper
-// bound UB on the best value (the best of the 8 x 8 pairs of smallest A_i and
+// bound UB on the best value (the best of the 8 x 8 pairs of eight of the smallest A_i and
 // B_j, evaluated exactly) leaves only the pairs whose lower bound reaches UB:
 // two fused multiply-adds and a compare per pair, no cross terms.  Those few
 // are evaluated exactly in float64 (||g - u_i + u_j||^2 / (P - p_i + p_j)^2,
@@ -163,6 +163,7 @@ struct SwapState {
 };
 
 constexpr int kSwapCand = 8192;  // surviving pairs kept per row (8192 and 16384 measured alike, 4096 11 % slower)
+constexpr int kSwapCandT = 1024;   // threads scoring a row's survivors (141 us a sweep of 1024 rows of 32,768 keys, 193 with 256)
 constexpr int kSwapSweepRows = 64;  // rows a fallback sweep takes at a time
 constexpr int kSwapSL = 16;      // keys per slice of the bound pass's whole-slice test (<= 32)
 constexpr int kSwapSort = 2048;  // kept keys ordered for the bound pass
@@ -1181,10 +1182,10 @@ swap_bound_kernel(int64_t n, int kk, int jn, SwapState s) {
 // the survivors (and the upper bound's own pair) evaluated exactly; the
 // winner goes to the first partial slot of the row, the others are cleared
 template <typename T>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(kSwapCandT)
 swap_cand_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, SwapState s) {
-    __shared__ double redv[4];
-    __shared__ int64_t redi[4];
+    __shared__ double redv[kSwapCandT / 64];
+    __shared__ int64_t redi[kSwapCandT / 64];
     __shared__ double gs[256], ms[256];
     const int64_t r = blockIdx.x;
     if (!s.st[r * 2]) return;
@@ -1487,7 +1488,7 @@ static hipError_t swap_large(const fw_rows &rows, int k, int max_iters, int32_t 
         launch_dots<T>(v, H, G, n, d, L.s, st);
         hipLaunchKernelGGL(swap_ub_kernel<T>, dim3((unsigned)R), dim3(256), 0, st, v, G, n, d, k, L.s);
         launch_bound(R, n, k, L.s, st);
-        hipLaunchKernelGGL(swap_cand_kernel<T>, dim3((unsigned)R), dim3(256), 0, st, v, G, n, d, L.s);
+        hipLaunchKernelGGL(swap_cand_kernel<T>, dim3((unsigned)R), dim3(kSwapCandT), 0, st, v, G, n, d, L.s);
         // the sweep takes only the listed rows
         const unsigned sweep_y = (unsigned)(R < kSwapSweepRows ? R : kSwapSweepRows);
         if (swap_mfma_ok(rows))  // the listed rows' sweep records
