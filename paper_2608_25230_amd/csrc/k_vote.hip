@@ -87,6 +87,9 @@ __device__ __forceinline__ V team_reduce(V v, V *red, int NW, Op op) {
 // Up to kVoteList keys: every wave picks its own s (each pick a wave reduction
 // of the lanes' best keys; the lane that held it looks for its next), and the
 // waves' lists are merged by counting ranks.  More: s picks of the whole team.
+// A NaN is never picked: where fewer than s keys are left, the entries without
+// one are 0 (a row with a NaN has no finite weight; its list only has to hold
+// keys).
 template <typename F>
 __device__ void team_top(F &&get, int64_t N, int s, int *out, int t, int NT, unsigned char *red) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, NW = NT >> 6, w0 = w / NW * NW;
@@ -129,6 +132,7 @@ __device__ void team_top(F &&get, int64_t N, int s, int *out, int t, int NT, uns
                 next();
             }
         }
+        for (int u = t; u < s; u += NT) out[u] = 0;
         __syncthreads();
         for (int c = t; c < NW * s; c += NT) {
             const int i = ci[w0 * s + c];
@@ -155,7 +159,7 @@ __device__ void team_top(F &&get, int64_t N, int s, int *out, int t, int NT, uns
             mi = ci[w0];
             for (int i = 1; i < NW; ++i)
                 if (top_ahead(cv[w0 + i], ci[w0 + i], mv, mi)) { mv = cv[w0 + i]; mi = ci[w0 + i]; }
-            if (t == 0) out[u] = mi >= 0 ? mi : 0;  // s <= n: a key is always found
+            if (t == 0) out[u] = mi >= 0 ? mi : 0;
             if (mi >= 0 && bi == mi) {
                 pv = mv;
                 pi = mi;

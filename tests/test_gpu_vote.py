@@ -99,6 +99,42 @@ def test_small_groups_fp32(torch_fw, cfg):
     print(cfg, t)
 
 
+@pytest.mark.parametrize("s", [3, 32, 40])  # the waves' lists up to 32, one team pick at a time beyond
+@pytest.mark.parametrize("gs", [1, 4, 6])   # one row; every row's weights resident; rows beyond the resident ones
+@pytest.mark.parametrize("what", ["query", "key", "mask"])
+def test_rows_without_finite_weights(torch_fw, what, gs, s):
+    """A NaN in one query row, an infinite key element, a bias that masks
+    every key: the voted keys are still keys, and the errors of a row without
+    finite weights are NaN.  Groups that the bad value does not reach keep
+    their bits."""
+    torch, fw = torch_fw
+    H, n, d, T = 2, 70, 16, 2
+    G = gs * T
+    rows = _fp32_rows(77, H, G, n, d, 2.0, 4.0)
+    clean = _run(torch, fw, rows, s, gs)
+    if what == "query":
+        rows.q[1, G - 1, 5] = np.nan  # the last query head at the last position
+    elif what == "key":
+        rows.k[1, 60, 3] = np.inf
+    else:
+        rows.bias[:] = -np.inf
+    out = _run(torch, fw, rows, s, gs)
+    v = out["vote_idx"]
+    assert v.min() >= 0 and v.max() < n
+    if what == "mask":
+        assert np.all(np.isnan(out["es_vote"])) and np.all(np.isnan(out["es_top"]))
+    elif what == "query":
+        assert np.isnan(out["es_vote"][1, G - 1]) and np.isnan(out["es_top"][1, G - 1])
+        assert same_bits(v[1, 0], clean["vote_idx"][1, 0])
+        assert same_bits(out["es_vote"][1, 0], clean["es_vote"][1, 0])
+    else:
+        top = rows.q[1, :, 3] > 0  # rows with an infinite logit
+        assert top.any() and np.all(np.isnan(out["es_top"][1, top]))
+    if what != "mask":
+        for name in clean:
+            assert same_bits(out[name][0], clean[name][0]), name
+
+
 def test_model_groups_bf16(torch_fw):
     torch, fw = torch_fw
     wl = W.pool_rows(seed=4, layers=1, kv_heads=2, q_per_kv=4, rows_per_q=6, n=1024)
