@@ -540,7 +540,9 @@ tiers_kernel(TierArgs a) {
         const int cw = d - c0 < CW ? d - c0 : CW;
         const int col = c0 + m16 * CPL;  // this lane's columns
         // byte offsets of the lane's values and logits in a block; past the end: reads zero
-        const uint32_t vcol = col < d ? (uint32_t)((kg * 8 * d + col) * (int)sizeof(T)) : 0x7FFFFFF0u;
+        // (far past every descriptor, and no step of a block wraps it)
+        const uint32_t vcol = col < d ? (uint32_t)((kg * 8 * d + col) * (int)sizeof(T)) : 0x7FFFFF00u;
+        const uint32_t kstep = (uint32_t)(d * (int)sizeof(T));
         const uint32_t vrow = live ? (uint32_t)((m16 * n + kg * 8) * 4) : 0xFFFFFFC0u;
         f32x4 acc[NT][CPL];
 #pragma unroll
@@ -553,24 +555,26 @@ tiers_kernel(TierArgs a) {
             // values of the lane's eight keys and their logits for its row.  With
             // a.vec by buffer loads: a descriptor per block (wave-uniform), so that
             // keys past the end and lanes without columns or row read zero and no
-            // per-key address is held.
+            // per-key address is held.  The key step is part of the vector offset:
+            // the range check leaves the scalar offset out.
             uint4 raw[8][LPK];
             float zz[8];
             if (a.vec) {
                 const int64_t left = n - blk * 32;
+                const uint32_t vo = opaque(vcol);  // eight sums per block rather than eight registers
                 const rsrc_t rv = make_rsrc(vh + blk * 32 * d, (uint32_t)((left < 32 ? left : 32) * d * (int)sizeof(T)));
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
 #pragma unroll
                     for (int l = 0; l < LPK; ++l) {
                         if (B16 && CPL == 4) {  // 8 bytes per key
-                            const auto x = __builtin_amdgcn_raw_buffer_load_b64(rv, vcol, e * d * (int)sizeof(T), 0);
+                            const auto x = __builtin_amdgcn_raw_buffer_load_b64(rv, vo + e * kstep, 0, 0);
                             const uint2 y = __builtin_bit_cast(uint2, x);
                             raw[e][l] = make_uint4(y.x, y.y, 0u, 0u);
                         } else {
                             // d is a multiple of 8: a lane with its first column has all of them
                             raw[e][l] = __builtin_bit_cast(
-                                uint4, __builtin_amdgcn_raw_buffer_load_b128(rv, vcol + l * 16, e * d * (int)sizeof(T), 0));
+                                uint4, __builtin_amdgcn_raw_buffer_load_b128(rv, vo + e * kstep + l * 16, 0, 0));
                         }
                     }
                 }

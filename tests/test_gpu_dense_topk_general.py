@@ -112,6 +112,25 @@ def test_values_that_are_not_finite(torch_fw, dtype):
     assert np.allclose(t2np(clean["o"])[0][:, cols], t2np(out["o"])[0][:, cols], rtol=0, atol=1e-5)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,d", [(33, 128), (1, 64), (70, 256), (2053, 72)])
+def test_values_behind_the_last_unit_are_not_read(torch_fw, dtype, n, d):
+    """A last block of fewer than seven keys: what lies behind the values of
+    the last unit changes no bit of the outputs (a NaN read there would send
+    the wave's sums to the key-by-key form, in another order)."""
+    torch, fw = torch_fw
+    rows = W.sink_rows(75, n, 2, 5, n, d, dtype, sink=4.0)
+    dev = fw.upload(rows)
+    size = dev["v"].numel()
+    got = []
+    for fill in (0.0, float("nan")):
+        flat = torch.full((size + 64 * d,), fill, dtype=dev["v"].dtype, device="cuda")
+        v = flat[:size].view(dev["v"].shape).copy_(dev["v"])
+        got.append(fw.dense_topk(dev["q"], dev["k"], v, sorted({1, (n + 2) // 3, n}), dev["scale"], dev["bias"]))
+    for name in ("o", "o_s", "gap", "dropped", "topk_idx"):
+        assert torch.equal(got[0][name], got[1][name]), name
+
+
 def test_noalloc_near_its_limit(torch_fw):
     """A call whose logits nearly fill the static scratch array still runs
     there (with fewer key splits), and gives what the workspace call gives."""
