@@ -246,8 +246,8 @@ fw_status dense_topk_launch(const fw_rows *rows, const fw::KsArg &k, float *o, f
         e = fw::launch_select(w.z, H * G, n, k, w.row_m, w.row_l, w.thr_key, w.thr_cut, topk_idx,
                               kmax, st);
     if (e == hipSuccess)
-        e = fw::launch_tiers(rows->dtype, rows->v, w.z, w.row_m, w.thr_key, w.thr_cut, H, G, n, d, k, o, o_s, gap,
-                             dropped, w.splits, w.part, w.part_m, st);
+        e = fw::launch_tiers(rows->dtype, rows->v, w.z, w.row_m, w.row_l, w.thr_key, w.thr_cut, H, G, n, d, k, o,
+                             o_s, gap, dropped, w.splits, w.part, w.part_m, st);
     return hip_status(e, "fw_dense_topk");
 }
 

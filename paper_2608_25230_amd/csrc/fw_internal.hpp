@@ -23,10 +23,10 @@ hipError_t launch_select(const float *z, int64_t R, int64_t n, const KsArg &ks, 
 // key ranges that launch_tiers' sums are split into; with more than one it
 // takes part [splits][R][n_ks + 1][d] and part_m [splits][R][n_ks + 1]
 int tiers_splits(int dtype, int64_t H, int64_t G, int64_t n);
-hipError_t launch_tiers(int dtype, const void *v, const float *z, const float *row_m, const uint32_t *thr_key,
-                        const int32_t *thr_cut, int64_t H, int64_t G, int64_t n, int d, const KsArg &ks, float *o,
-                        float *o_s, float *gap, float *dropped, int splits, float *part, float *part_m,
-                        hipStream_t st);
+hipError_t launch_tiers(int dtype, const void *v, const float *z, const float *row_m, const float *row_l,
+                        const uint32_t *thr_key, const int32_t *thr_cut, int64_t H, int64_t G, int64_t n, int d,
+                        const KsArg &ks, float *o, float *o_s, float *gap, float *dropped, int splits, float *part,
+                        float *part_m, hipStream_t st);
 
 // k_topk_fused.hip -- one-kernel path for bf16, d = 128, n in {1024, 2048, 4096}
 bool fused_topk_supported(const fw_rows &rows, const KsArg &ks);

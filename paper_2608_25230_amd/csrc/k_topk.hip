@@ -394,7 +394,7 @@ select_kernel(const float *__restrict__ z, int64_t R, int64_t n, KsArg ks, float
 // ---------------------------------------------------------------------------
 struct TierArgs {
     const void *v;
-    const float *z, *row_m;
+    const float *z, *row_m, *row_l;
     const uint32_t *thr_key;
     const int32_t *thr_cut;
     int64_t H, G, n;
@@ -404,6 +404,13 @@ struct TierArgs {
     float *part;    // [splits][R][NT][d] tier sums, splits > 1
     float *part_m;  // [splits][R][NT] tier masses
 };
+
+// The power of two by which a row's weights exp(z - m) are scaled so that they
+// sum to at most one (l >= 1 is their sum): no tier sum exceeds the largest
+// value, and a quotient of tier sums keeps its bits.
+__device__ __forceinline__ float weight_scale(float l) {
+    return __uint_as_float((253u - (__float_as_uint(l) >> 23)) << 23);
+}
 
 // Outputs of row r for the columns c = lane + 64 x, x < NC (those below cw) of
 // a slice at c0, from its tier sums T(t, x) and masses; returns through ss the
@@ -521,19 +528,22 @@ tiers_kernel(TierArgs a) {
     const int64_t b0 = sp * per, b1 = b0 + per < blocks ? b0 + per : blocks;
     const T *vh = (const T *)a.v + h * n * (int64_t)d;
     const int64_t r = r0 + m16;
-    const bool live = m16 < rows;
-    const float *zr = a.z + (live ? r : r0) * n;
-    const float m = live ? a.row_m[r] : 0.f;
+    // a row whose weights' sum is NaN takes no part: its masses start as that NaN,
+    // which reaches all of its outputs
+    const bool there = m16 < rows;
+    const float l = there ? a.row_l[r] : 1.f, m = there ? a.row_m[r] : 0.f, wsc = weight_scale(l);
+    const bool live = there && l < INFINITY;
+    const float *zr = a.z + (there ? r : r0) * n;
     unsigned long long thr[NT - 1];
 #pragma unroll
     for (int t = 0; t < NT - 1; ++t)
-        thr[t] = live ? ((unsigned long long)a.thr_key[r * (NT - 1) + t] << 32) |
+        thr[t] = there ? ((unsigned long long)a.thr_key[r * (NT - 1) + t] << 32) |
                             (0xFFFFFFFFu - (uint32_t)a.thr_cut[r * (NT - 1) + t])
                       : 0ull;
     if (tid < 16 * NT) ss_s[tid / NT][tid % NT] = 0.f;
     float mass[NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) mass[t] = 0.f;
+    for (int t = 0; t < NT; ++t) mass[t] = l < INFINITY ? 0.f : l;
 
 #pragma nounroll
     for (int c0 = 0; c0 < d; c0 += CW) {
@@ -543,7 +553,7 @@ tiers_kernel(TierArgs a) {
         // (far past every descriptor, and no step of a block wraps it)
         const uint32_t vcol = col < d ? (uint32_t)((kg * 8 * d + col) * (int)sizeof(T)) : 0x7FFFFF00u;
         const uint32_t kstep = (uint32_t)(d * (int)sizeof(T));
-        const uint32_t vrow = live ? (uint32_t)((m16 * n + kg * 8) * 4) : 0xFFFFFFC0u;
+        const uint32_t vrow = there ? (uint32_t)((m16 * n + kg * 8) * 4) : 0xFFFFFFC0u;
         f32x4 acc[NT][CPL];
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
@@ -604,7 +614,7 @@ tiers_kernel(TierArgs a) {
 #pragma unroll
                         for (int i = 0; i < CPL; ++i) to[i] = x[i];
                     }
-                    zz[e] = (live && j0 + e < n) ? zr[j0 + e] : 0.f;
+                    zz[e] = (there && j0 + e < n) ? zr[j0 + e] : 0.f;
                 }
             }
             float p[8];
@@ -612,7 +622,7 @@ tiers_kernel(TierArgs a) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int64_t j = j0 + e;
-                p[e] = (live && j < n) ? expf(zz[e] - m) : 0.f;
+                p[e] = (live && j < n) ? expf(zz[e] - m) * wsc : 0.f;
                 const unsigned long long u =
                     ((unsigned long long)ord_key(zz[e]) << 32) | (0xFFFFFFFFu - (uint32_t)j);
                 tier[e] = NT - 1;
@@ -717,10 +727,11 @@ tiers_kernel(TierArgs a) {
                 const int rr = 4 * kg + i4;
                 if (rr >= rows) continue;
                 const int64_t rw = r0 + rr;
-                const float mr = a.row_m[rw];
+                const float mr = a.row_m[rw], lr = a.row_l[rw], wr = weight_scale(lr);
+                if (!(lr < INFINITY)) continue;
                 for (int64_t blk = b0 + w; blk < b1; blk += 4) {
                     for (int64_t j = blk * 32; j < blk * 32 + 32 && j < n; ++j) {
-                        const float x = a.z[rw * n + j], pj = expf(x - mr);
+                        const float x = a.z[rw * n + j], pj = expf(x - mr) * wr;
                         const uint32_t u = ord_key(x);
                         int tj = NT - 1;
                         for (int t = NT - 2; t >= 0; --t) {
@@ -935,14 +946,15 @@ static void tiers_nt(const TierArgs &a, hipStream_t st) {
     }
 }
 
-hipError_t launch_tiers(int dtype, const void *v, const float *z, const float *row_m, const uint32_t *thr_key,
-                        const int32_t *thr_cut, int64_t H, int64_t G, int64_t n, int d, const KsArg &ks, float *o,
-                        float *o_s, float *gap, float *dropped, int splits, float *part, float *part_m,
-                        hipStream_t st) {
+hipError_t launch_tiers(int dtype, const void *v, const float *z, const float *row_m, const float *row_l,
+                        const uint32_t *thr_key, const int32_t *thr_cut, int64_t H, int64_t G, int64_t n, int d,
+                        const KsArg &ks, float *o, float *o_s, float *gap, float *dropped, int splits, float *part,
+                        float *part_m, hipStream_t st) {
     TierArgs a{};
     a.v = v;
     a.z = z;
     a.row_m = row_m;
+    a.row_l = row_l;
     a.thr_key = thr_key;
     a.thr_cut = thr_cut;
     a.H = H;

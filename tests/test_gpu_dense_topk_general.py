@@ -113,6 +113,47 @@ def test_values_that_are_not_finite(torch_fw, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("H,n", [(1, 300), (1, 4999), (600, 40)])  # one key range, several, one per workgroup
+def test_large_values_and_many_keys(torch_fw, dtype, H, n):
+    """Values near float32's largest over keys of nearly equal weight: the
+    outputs are means of values, so they are finite, and sums of the weights
+    unscaled would not be."""
+    torch, fw = torch_fw
+    rows = W.sink_rows(76, n, H, 3, n, 64, dtype, sink=0.0)
+    rows.q[:] = 0
+    mag = np.float32(1.5 * 2.0 ** 126)
+    rows.v[:] = W.bf16_bits(np.full(rows.v.shape, mag, np.float32)) if dtype == "bf16" else mag
+    rows.v[:, ::2, 1] = rows.v[0, 0, 0] ^ 0x8000 if dtype == "bf16" else -mag
+    out, _ = _run(torch, fw, rows, (n // 4, n // 2))
+    o, o_s = t2np(out["o"]), t2np(out["o_s"])
+    # a sum of at most n weights, each of the tier's masses with it: 2 n roundings
+    tol = 2 * n * 2.0 ** -24
+    cols = np.arange(64) != 1
+    assert np.all(np.abs(o[..., cols] / mag - 1) <= tol) and np.all(np.abs(o_s[..., cols] / mag - 1) <= tol)
+    assert np.all(np.abs(o[..., 1] / mag + (n % 2) / n) <= tol)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_not_a_number_in_a_row_reaches_all_its_outputs(torch_fw, dtype):
+    """A NaN query element: its row has no weights, so every output of that
+    row but the indices is NaN; the other rows keep their bits."""
+    torch, fw = torch_fw
+    n, ks = 700, (3, 90)
+    rows = W.sink_rows(77, 4, 1, 6, n, 64, dtype, sink=4.0)
+    clean, _ = _run(torch, fw, rows, ks)
+    rows.q[0, 2, 5] = 0x7FC0 if dtype == "bf16" else np.nan
+    out, _ = _run(torch, fw, rows, ks)
+    others = [0, 1, 3, 4, 5]
+    assert np.all(np.isnan(t2np(out["o"])[0, 2])) and np.all(np.isnan(t2np(out["o_s"])[:, 0, 2]))
+    assert np.all(np.isnan(t2np(out["dropped"])[:, 0, 2]))
+    idx = t2np(out["topk_idx"])
+    assert idx.min() >= 0 and idx.max() < n
+    assert torch.equal(out["o"][:, others], clean["o"][:, others])
+    for name in ("o_s", "gap", "dropped"):
+        assert torch.equal(out[name][:, :, others], clean[name][:, :, others]), name
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("n,d", [(33, 128), (1, 64), (70, 256), (2053, 72)])
 def test_values_behind_the_last_unit_are_not_read(torch_fw, dtype, n, d):
     """A last block of fewer than seven keys: what lies behind the values of
