@@ -296,12 +296,19 @@ __global__ void __launch_bounds__(PT) pool_row_kernel(PoolArgs a) {
 
     // top keys in rank order (z desc, j asc); every budget's A*_s is a prefix
     wave_top(zz, N, a.Smax, rank, redd, redi);
-    for (int t = tid; t < a.Smax; t += NT) rk[rank[t]] = (unsigned char)t;
-    // weights in place of the logits; each budget's dropped mass summed over
-    // its dropped keys themselves
     double lsum = 0.0;
     for (int64_t j = tid; j < N; j += NT) lsum += exp(zz[j] - zmax);
     lsum = block_sum(lsum, redd);
+    // a NaN or +inf logit, or every key masked: no weight is a number, NaNs have
+    // no order, and the row's pools only have to be distinct keys
+    if (!(lsum < INFINITY)) {
+        for (int t = tid; t < a.Smax; t += NT) rank[t] = t;
+        __syncthreads();
+    }
+    for (int t = tid; t < a.Smax; t += NT) rk[rank[t]] = (unsigned char)t;
+    __syncthreads();
+    // weights in place of the logits; each budget's dropped mass summed over
+    // its dropped keys themselves
     double drop[kMaxBudgets];
 #pragma unroll
     for (int b = 0; b < kMaxBudgets; ++b) drop[b] = 0.0;
@@ -385,6 +392,12 @@ __global__ void __launch_bounds__(PT) pool_row_kernel(PoolArgs a) {
     for (int b = 1; b < nb; ++b) smin = a.b[b].s < smin ? a.b[b].s : smin;
     for (int b = 0; b < nb; ++b) me = a.b[b].extra + a.b[b].s - smin > me ? a.b[b].extra + a.b[b].s - smin : me;
     wave_top(ee, N, me, eord, redd, redi, rk, smin);
+    if (!(s2 < INFINITY)) {  // errors that are NaN (or all infinite)
+        if (tid == 0)
+            for (int j = 0, t = 0; t < me; ++j)  // extra + s <= N: me keys are left
+                if (rk[j] >= smin) eord[t++] = j;
+        __syncthreads();
+    }
     for (int b = 0; b < nb; ++b) {
         const PoolBudget &B = a.b[b];
         const int s = B.s, P = B.P;
@@ -459,7 +472,9 @@ __global__ void __launch_bounds__(PT) pool_row_kernel(PoolArgs a) {
             }
             if (tid == 0) *(uint64_t *)(inst + I.seed) = seed;
         }
-        const uint64_t best = B.direct ? enum_complement(Gm, ps, P, P - s, cv, redd, redm) : 0ull;
+        // (0: every set's value is NaN; A*_s stands for it, as in the walk)
+        uint64_t best = B.direct ? enum_complement(Gm, ps, P, P - s, cv, redd, redm) : 0ull;
+        best = best ? best : seed;
 
         // Balancing within the pool on wave 0 alone (P <= 64 keys, one per
         // lane, no workgroup barrier), while waves 1 and 2 take the reported
@@ -565,12 +580,15 @@ __global__ void __launch_bounds__(PT) pool_row_kernel(PoolArgs a) {
                 return v;
             };
             int j0;
-            wave_argmin(inP ? Yd[x * P + x] : 0.0, j0);  // the key nearest mu
+            const double yxx = inP ? Yd[x * P + x] : 0.0;
+            // a row with a NaN takes no step (its lanes would follow different keys)
+            const int most = __ballot(yxx != yxx) ? 0 : a.fw_iters;
+            wave_argmin(yxx == yxx ? yxx : INFINITY, j0);  // the key nearest mu
             double wx = x == j0 ? 1.0 : 0.0;
             double tx = inP ? Yd[j0 * P + x] : 0.0;
             uint64_t sup = 1ull << j0;
             int steps = 0;
-            while (steps < a.fw_iters) {
+            while (steps < most) {
                 int j;
                 const double tj = wave_argmin(tx, j);
                 const double q = wave_sum(wx * tx);

@@ -278,7 +278,7 @@ __device__ inline void wave_top_scan(const double *vals, int64_t N, int M, doubl
 
 // The M (<= 64) largest values of vals[0, N) in the order (value desc,
 // index asc), keys with skip[j] < smin left out (no skip: all keys), their
-// indices into out[0, M).  Each wave takes the next best of its own keys M
+// indices into out[0, M), whose entries are not all set when a value is NaN.  Each wave takes the next best of its own keys M
 // times (shuffles only, no workgroup barrier), then the waves' lists are
 // merged by counting ranks.  cv, ci: LDS scratch of (blockDim.x / 64) M
 // entries.

@@ -132,6 +132,44 @@ def _fp32_rows(seed, H, G, n, d, temp=1.0, sink=0.0):
     return W.Rows(W.F32, q, K, V, np.full(H, 1.0 / math.sqrt(d), np.float32), bias)
 
 
+@pytest.mark.parametrize("n", [70, 4200])  # top keys from registers, and rescanned from LDS
+@pytest.mark.parametrize("what", ["query", "key", "mask"])
+def test_rows_without_finite_weights(torch_fw, what, n):
+    """A NaN in one query row, an infinite key element, a bias that masks
+    every key: pools of distinct keys, sets drawn from them, and NaN errors;
+    rows that the bad value does not reach keep their bits."""
+    torch, fw = torch_fw
+    rows = W.sink_rows(81, n, 2, 3, n, 20, "f32", sink=4.0)
+    budgets = ((4, 6), (8, 2), (5, 0))  # walked, enumerated in the row kernel, one set
+    clean = _run(torch, fw, rows, budgets, 8)
+    if what == "query":
+        rows.q[1, 2, 5] = np.nan
+        bad = [(1, 2)]
+    elif what == "key":
+        rows.k[1, 60, 3] = np.inf
+        bad = [(1, g) for g in range(3) if rows.q[1, g, 3] > 0]
+    else:
+        rows.bias[:] = -np.inf
+        bad = [(h, g) for h in range(2) for g in range(3)]
+    out = _run(torch, fw, rows, budgets, 8)
+    same = [(0, g) for g in range(3)] if what != "mask" else []
+    if what == "query":
+        same += [(1, 0), (1, 1)]
+    for (s, extra), o, c in zip(budgets, out, clean):
+        for h in range(2):
+            for g in range(3):
+                pool = o["pool_idx"][h, g]
+                assert pool.min() >= 0 and pool.max() < n and np.unique(pool).size == s + extra
+        for h, g in bad:
+            pool = set(o["pool_idx"][h, g].tolist())
+            for name in ("best_idx", "bal_idx", "geo_idx"):
+                assert set(o[name][h, g].tolist()) <= pool, name
+            assert np.isnan(o["stats"][h, g, STATS.index("es_top")])
+        for h, g in same:
+            for name in ("pool_idx", "best_idx", "bal_idx", "geo_idx", "n_swaps", "stats"):
+                assert same_bits(o[name][h, g], c[name][h, g]), name
+
+
 def test_example_2_3_pool_on_gpu(torch_fw):
     """Example 2.3 as an instance (q = 0, bias = log p): the candidate set with
     one extra key is every key, ES_pool = 9/22 at {0, 2}, kappa_hat = 11/9,
