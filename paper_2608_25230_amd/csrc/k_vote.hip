@@ -24,7 +24,6 @@ namespace fw {
 
 namespace {
 
-constexpr int VT = 512;        // threads per group workgroup
 constexpr int kVoteList = 32;  // sets up to this size are picked by waves and merged
 
 struct VoteLds {
@@ -117,7 +116,7 @@ __device__ void team_top(F &&get, int64_t N, int s, int *out, int t, int NT, uns
     __syncthreads();
     if (s <= kVoteList) {
         double *cv = (double *)red;                            // [waves][s]
-        int *ci = (int *)(red + (VT / 64) * kVoteList * 8);    // [waves][s]
+        int *ci = (int *)(red + 8 * kVoteList * 8);              // [waves][s], at most eight waves
         for (int u = 0; u < s; ++u) {
             double mv;
             int mi;
@@ -190,8 +189,8 @@ __device__ double es_list(const T *vh, int d, const int *keys, const double *pk,
 
 }  // namespace
 
-template <typename T, int RB>
-__global__ void __launch_bounds__(VT) vote_group_kernel(VoteArgs a) {
+template <typename T, int RB, int VT>
+__global__ void __launch_bounds__(VT, 2) vote_group_kernel(VoteArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int NT = VT / RB, NW = NT / 64;  // a row's team
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), team = tid / NT, t = tid % NT;
@@ -254,9 +253,10 @@ __global__ void __launch_bounds__(VT) vote_group_kernel(VoteArgs a) {
                     raw[u] = (j < N && has) ? RowVec<T>::raw(kh + j * d, gi * VEC) : make_uint4(0u, 0u, 0u, 0u);
                 }
             };
-            load((int64_t)w * KPW);
+            if constexpr (RB > 1) load((int64_t)w * KPW);
 #pragma nounroll
             for (int64_t j0 = (int64_t)w * KPW; j0 < N; j0 += stride * U) {
+                if constexpr (RB == 1) load(j0);  // both sets of 16 keys would spill
                 double acc[16];  // [key][row]
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -271,7 +271,7 @@ __global__ void __launch_bounds__(VT) vote_group_kernel(VoteArgs a) {
                         for (int rr = 0; rr < RB; ++rr) acc[u * RB + rr] = fma(xr[rr][i], xd, acc[u * RB + rr]);
                     }
                 }
-                load(j0 + stride * U);  // in flight during the reductions
+                if constexpr (RB > 1) load(j0 + stride * U);  // in flight during the reductions
                 if (GL == 16) {
                     // transposed: at each exchange a lane gives away half of its
                     // sums, and lane i ends with sum i of its group
@@ -505,11 +505,23 @@ hipError_t launch_vote(const fw_rows &rows, int s, int gs, int32_t *vote_idx, fl
     const int rb = vote_rows(rows.n, (int)rows.d, gs, s);
     const size_t lds = vote_lds(rows.n, (int)rows.d, gs, s, rb).total;
     const dim3 g((unsigned)(rows.H * (rows.G / gs)));
-#define FW_VOTE(T)                                                                                        \
-    switch (rb) {                                                                                         \
-        case 4: hipLaunchKernelGGL((vote_group_kernel<T, 4>), g, dim3(VT), lds, st, a); break;            \
-        case 2: hipLaunchKernelGGL((vote_group_kernel<T, 2>), g, dim3(VT), lds, st, a); break;            \
-        default: hipLaunchKernelGGL((vote_group_kernel<T, 1>), g, dim3(VT), lds, st, a); break;           \
+    // One row at a time: four waves per group, two workgroups on a CU (one in its
+    // serial picks, the other reading), where there are groups and LDS for two, and
+    // for a few keys in whole chunks, whose picks eight waves' lists only lengthen;
+    // else eight.  Groups of one, s = 8, bf16 rows of 128 columns, four waves
+    // against eight: 1536 of 4096 keys 626 us against 835 (eight with a prefetch
+    // that spilled); 256 of 4096 178 against 134, of 130 32 against 45; 4 of 130
+    // keys of 100 columns 42 against 35.
+    const bool chunks = rows.d % (rows.dtype == FW_BF16 ? 8 : 4) == 0;
+    const bool four = (rows.n <= 256 && chunks) || (lds <= 80 * 1024 && g.x > 256);
+#define FW_VOTE_K(T, RB, VT) hipLaunchKernelGGL((vote_group_kernel<T, RB, VT>), g, dim3(VT), lds, st, a)
+#define FW_VOTE(T)                               \
+    switch (rb) {                                \
+        case 4: FW_VOTE_K(T, 4, 512); break;     \
+        case 2: FW_VOTE_K(T, 2, 512); break;     \
+        default:                                 \
+            if (four) FW_VOTE_K(T, 1, 256);      \
+            else FW_VOTE_K(T, 1, 512);           \
     }
     if (rows.dtype == FW_BF16) {
         FW_VOTE(uint16_t)
@@ -517,6 +529,7 @@ hipError_t launch_vote(const fw_rows &rows, int s, int gs, int32_t *vote_idx, fl
         FW_VOTE(float)
     }
 #undef FW_VOTE
+#undef FW_VOTE_K
     return hipGetLastError();
 }
 

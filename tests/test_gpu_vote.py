@@ -89,6 +89,8 @@ def test_group_of_one_votes_its_own_top_mass_set(torch_fw):
     (1, 2, 7000, 20, 9, 2, 1.0, 0.0),  # rows too long for four at a time
     (1, 5, 7000, 21, 4, 5, 1.0, 0.0),  # one at a time, one element per lane
     (2, 1, 5, 7, 5, 1, 1.0, 0.0),      # every key kept, fewer keys than threads
+    (2, 2, 257, 64, 40, 1, 1.5, 4.0),  # groups of one: eight waves past 256 keys
+    (65, 4, 300, 16, 9, 1, 2.0, 0.0),  # and four when there are more than 256 groups
 ])
 def test_small_groups_fp32(torch_fw, cfg):
     torch, fw = torch_fw
