@@ -228,16 +228,17 @@ swap_init_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, int kk, S
     }
     __syncthreads();
     list_set(inS, n, scan, s.Sl + r * kk);
-    // mu = sum_j p_j v_j, float64: each lane its columns over the keys it
-    // visits, the lane groups' sums added in order
+    // mu = sum_j p_j v_j, float64
+    constexpr int VEC = RowVec<T>::VEC;
+    const bool vec = d % VEC == 0;
     double *mu = s.mu + r * d;
-    {
-        constexpr int VEC = RowVec<T>::VEC;
-        const bool vec = d % VEC == 0;
-        const int GL = vec ? group_lanes(d, VEC) : 64, lane = tid & 63, gi = vec ? lane % GL : lane;
-        double part[8];
+    if (vec) {
+        // each lane its columns over the keys it visits, the lane groups' sums
+        // added in order
+        const int GL = group_lanes(d, VEC), lane = tid & 63, gi = lane % GL;
+        double part[VEC];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) part[i] = 0.0;
+        for (int i = 0; i < VEC; ++i) part[i] = 0.0;
         for_keys(vh, n, d, [&](int64_t j, int, int, auto &&walk) {
             if (j < 0) return;
             const double pj = (double)p[j];
@@ -248,20 +249,54 @@ swap_init_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, int kk, S
         for (int rnd = 0; rnd < NT / 64 * (64 / GL); ++rnd) {
             if ((tid >> 6) * (64 / GL) + lane / GL == rnd) {
 #pragma unroll
-                for (int i = 0; i < (VEC > 4 ? VEC : 4); ++i) {
-                    const int c = vec ? gi * VEC + i : gi + 64 * i;
-                    if (c < d && (!vec || i < VEC)) mu_s[c] += part[i];
-                }
+                for (int i = 0; i < VEC; ++i)
+                    if (gi * VEC + i < d) mu_s[gi * VEC + i] += part[i];
             }
             __syncthreads();
         }
-        for (int c = tid; c < d; c += NT) mu[c] = mu_s[c];
+    } else {
+        // 16 key lanes x 16 groups of eight columns, the key lanes' sums added by a
+        // butterfly, and 16 lanes per key below: with a wave per key and one
+        // element per lane and load, the reductions bound it (one row of 16,000
+        // bf16 keys, two sweeps: 20 columns 1.53 ms a call against 5.36, 100
+        // columns 2.10 against 6.22)
+        const int jl = tid & 15, cg = tid >> 4;
+        for (int c0 = 8 * cg; c0 < d; c0 += 128) {
+            double acc[8];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) acc[x] = 0.0;
+            for (int64_t j = jl; j < n; j += 16) {
+                const double pj = (double)p[j];
+                float xv[8];
+                load8(vh + j * d, c0, d, xv);
+#pragma unroll
+                for (int x = 0; x < 8; ++x)
+                    if (c0 + x < d) acc[x] = fma(pj, (double)xv[x], acc[x]);
+            }
+#pragma unroll
+            for (int x = 0; x < 8; ++x) {
+#pragma unroll
+                for (int off = 1; off < 16; off <<= 1) acc[x] += __shfl_xor(acc[x], off);
+            }
+            if (jl == 0) {
+#pragma unroll
+                for (int x = 0; x < 8; ++x)
+                    if (c0 + x < d) mu_s[c0 + x] = acc[x];
+            }
+        }
+        __syncthreads();
     }
+    for (int c = tid; c < d; c += NT) mu[c] = mu_s[c];
     __syncthreads();
     double mu2 = 0.0;
     for (int cc = 0; cc < d; ++cc) mu2 += mu[cc] * mu[cc];
     // w_j = v_j . mu and ||u_j||^2 = p_j^2 ||v_j - mu||^2
-    {
+    const auto put_bq = [&](int64_t j, double du) {
+        const float b = (float)((double)p[j] * (double)p[j] * du);
+        s.bq[r * n + j] = b;
+        s.rj[r * n + j] = sqrtf(b);
+    };
+    if (vec) {
         double xr[8];  // this lane's columns of mu
 #pragma unroll
         for (int i = 0; i < 8; ++i) xr[i] = 0.0;
@@ -275,11 +310,29 @@ swap_init_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, int kk, S
                 const double y = (double)x - xr[slot];
                 return fma(y, y, acc);
             },
-            [&](int64_t j, double du) {
-                const float b = (float)((double)p[j] * (double)p[j] * du);
-                s.bq[r * n + j] = b;
-                s.rj[r * n + j] = sqrtf(b);
-            });
+            put_bq);
+    } else {
+        // 16 lanes per key
+        const int jl = tid >> 4, cl = tid & 15;
+        for (int64_t j0 = 0; j0 < n; j0 += NT / 16) {
+            const int64_t j = j0 + jl;
+            double dw = 0.0, du = 0.0;
+            if (j < n)
+                for (int cc = cl; cc < d; cc += 16) {
+                    const double x = (double)Elem<T>::load(vh, j * d + cc), m = mu_s[cc];
+                    dw = fma(x, m, dw);
+                    du = fma(x - m, x - m, du);
+                }
+#pragma unroll
+            for (int off = 1; off < 16; off <<= 1) {
+                dw += __shfl_xor(dw, off);
+                du += __shfl_xor(du, off);
+            }
+            if (j < n && cl == 0) {
+                s.w[r * n + j] = (float)dw;
+                put_bq(j, du);
+            }
+        }
     }
     // g = sum_{a in S} u_a, P = p(S): 16 kept-key lanes x 16 column groups,
     // the key lanes' sums added by a butterfly
