@@ -18,6 +18,37 @@ namespace {
 constexpr int kChunk = 512;   // keys per workgroup in the logit passes
 constexpr int kRowGrp = 16;   // window rows per LDS tile
 constexpr int kSortThreads = 1024;
+
+// rows of fewer columns take a key per thread (window_thin_kernel)
+template <typename T> constexpr int thin_cols() { return sizeof(T) == 2 ? 24 : 16; }
+
+// words per row of a staged key tile of ch chunks: four times an odd number, so
+// that 16 rows' reads of a chunk meet no bank twice
+__host__ __device__ constexpr int window_rs(int ch) { return ch / 4 % 2 ? ch : ch + 4; }
+
+// Per window row of the group (16 threads each): the largest of the chunk's
+// logits zt and the sum of exponentials over it, into part_m and part_s.
+__device__ __forceinline__ void chunk_stats(const float (*zt)[kChunk + 1], float *red, int gn, int64_t row0, int nchunks,
+                                            int ch, float *part_m, float *part_s) {
+    const int tid = threadIdx.x, g = tid / 16, l = tid % 16;
+    float m = -INFINITY;
+    for (int jl = l; jl < kChunk; jl += 16) m = fmaxf(m, zt[g][jl]);
+    red[tid] = m;
+    __syncthreads();
+    m = red[g * 16];
+    for (int t = 1; t < 16; ++t) m = fmaxf(m, red[g * 16 + t]);
+    __syncthreads();
+    float s = 0.f;
+    for (int jl = l; jl < kChunk; jl += 16) s += (zt[g][jl] == -INFINITY) ? 0.f : expf(zt[g][jl] - m);
+    red[tid] = s;
+    __syncthreads();
+    if (l == 0 && g < gn) {
+        float st = 0.f;
+        for (int t = 0; t < 16; ++t) st += red[g * 16 + t];
+        part_m[(row0 + g) * nchunks + ch] = m;
+        part_s[(row0 + g) * nchunks + ch] = st;
+    }
+}
 }  // namespace
 
 // Pass 1 (MODE 0) and pass 3 (MODE 1) share the logit computation: a
@@ -27,8 +58,10 @@ constexpr int kSortThreads = 1024;
 // multiply-adds over the columns in order (see scores_kernel), and the sums
 // over keys and rows below run in one fixed order, so the scores and the order
 // built on them do not depend on the tiling.  Takes every window that
-// k_window.hip does not.  64 cells of 64 rows of 8192 float32 keys of 128
-// columns: 0.42 ms a call, 1.90 ms with one thread per key reading its own row.
+// k_window.hip and window_thin_kernel do not.  64 cells of 64 rows of 8192
+// float32 keys of 128 columns: 0.42 ms a call, 1.90 ms with one thread per key
+// reading its own row; of 20,000 keys of 129 to 192 bf16 columns (DC = 6) 2.09
+// ms at 129, 2.55 padded to 256.
 template <typename T, int DC, int MODE>
 __global__ void __launch_bounds__(256)
 window_logits_kernel(const T *__restrict__ q, const T *__restrict__ k, const float *__restrict__ scale,
@@ -40,7 +73,7 @@ window_logits_kernel(const T *__restrict__ q, const T *__restrict__ k, const flo
     constexpr int E = 16 / (int)sizeof(T);  // elements per 16-byte chunk
     constexpr int CH = DC * 32 / E;         // chunks per row
     constexpr int LD = CH / 4;              // loads per lane and tile (16 rows x CH chunks / 64)
-    constexpr int RS = CH + 4;              // words per row and kg: no bank conflicts on the reads
+    constexpr int RS = window_rs(CH);       // words per row and kg
     extern __shared__ __align__(16) uint32_t lds_w[];  // [wave][kg][row][chunk]
     __shared__ float zt[MODE == 0 ? kRowGrp : 1][kChunk + 1];  // logits; MODE 1: the keys' sums
     __shared__ float red[256];
@@ -64,6 +97,8 @@ window_logits_kernel(const T *__restrict__ q, const T *__restrict__ k, const flo
             if (j >= rows || c >= d) continue;
             if (vec) {
                 raw[i] = *(const uint4 *)(base + j * d + c);
+            } else if (B16 && c + E <= d) {  // a whole chunk at any alignment, not eight loads
+                __builtin_memcpy(&raw[i], base + j * d + c, 16);
             } else {
                 T x[E];
 #pragma unroll
@@ -158,26 +193,7 @@ window_logits_kernel(const T *__restrict__ q, const T *__restrict__ k, const flo
         }
         if (MODE == 0) {
             __syncthreads();
-            // 16 threads per row: local max, then local sum, over 512 keys
-            const int g = tid / 16, l = tid % 16;
-            float m = -INFINITY;
-            for (int jl = l; jl < kChunk; jl += 16) m = fmaxf(m, zt[g][jl]);
-            red[tid] = m;
-            __syncthreads();
-            m = red[g * 16];
-            for (int t = 1; t < 16; ++t) m = fmaxf(m, red[g * 16 + t]);
-            __syncthreads();
-            float s = 0.f;
-            for (int jl = l; jl < kChunk; jl += 16) s += (zt[g][jl] == -INFINITY) ? 0.f : expf(zt[g][jl] - m);
-            red[tid] = s;
-            __syncthreads();
-            if (l == 0 && g < gn) {
-                float st = 0.f;
-                for (int t = 0; t < 16; ++t) st += red[g * 16 + t];
-                const int64_t row = h * G + g0 + g;
-                part_m[row * nchunks + ch] = m;
-                part_s[row * nchunks + ch] = st;
-            }
+            chunk_stats(zt, red, gn, h * G + g0, nchunks, ch, part_m, part_s);
         }
         __syncthreads();
     }
@@ -185,6 +201,77 @@ window_logits_kernel(const T *__restrict__ q, const T *__restrict__ k, const flo
         const float invG = 1.0f / (float)G;
         for (int e = tid; e < kChunk; e += 256)
             if (j0 + e < n) importance[h * n + j0 + e] = zt[0][e] * invG;
+    }
+}
+
+// The same passes for rows of fewer than thin_cols columns, two keys per
+// thread: the matrix tiles would be mostly padding and the sums over a key's
+// rows cross lanes.  Same bits.  64 cells of 64 rows of 20,000 keys, a call, here
+// and on the tiles: 4 bf16 columns 278 us and 549 (padded to 64); 20 bf16 columns
+// 405 and 416, 30 508 and 427; 16 float32 columns 393 and 408, 20 486 and 414.
+template <typename T, int MODE>
+__global__ void __launch_bounds__(256)
+window_thin_kernel(const T *__restrict__ q, const T *__restrict__ k, const float *__restrict__ scale,
+                   const float *__restrict__ bias, int64_t G, int64_t n, int d, int nchunks,
+                   float *__restrict__ part_m, float *__restrict__ part_s, const float *__restrict__ row_m,
+                   const float *__restrict__ row_il, float *__restrict__ importance) {
+    __shared__ float Qs[kRowGrp][thin_cols<T>()];
+    __shared__ float zt[MODE == 0 ? kRowGrp : 1][kChunk + 1];
+    __shared__ float red[256];
+    const int tid = threadIdx.x;
+    const int64_t h = (uint32_t)blockIdx.x / (uint32_t)nchunks;
+    const int ch = (uint32_t)blockIdx.x % (uint32_t)nchunks;
+    const int64_t j0 = (int64_t)ch * kChunk;
+    const T *qh = q + h * G * d;
+    const T *kh = k + h * n * d;
+    const float sc = scale ? scale[h] : (float)(1.0 / sqrt((double)d));
+    float racc[2] = {0.f, 0.f};
+    for (int64_t g0 = 0; g0 < G; g0 += kRowGrp) {
+        const int gn = (G - g0 < kRowGrp) ? (int)(G - g0) : kRowGrp;
+        for (int e = tid; e < kRowGrp * d; e += 256) {
+            const int rr = e / d, cc = e % d;
+            Qs[rr][cc] = (rr < gn) ? Elem<T>::load(qh, (g0 + rr) * d + cc) : 0.f;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int jl = tid + 256 * u;
+            const int64_t j = j0 + jl;
+            float acc[kRowGrp];
+#pragma unroll
+            for (int g = 0; g < kRowGrp; ++g) acc[g] = 0.f;
+            if (j < n) {
+                for (int c = 0; c < d; ++c) {
+                    const float kv = Elem<T>::load(kh, j * d + c);
+#pragma unroll
+                    for (int g = 0; g < kRowGrp; ++g) acc[g] = fmaf(Qs[g][c], kv, acc[g]);
+                }
+            }
+            const float bj = (bias && j < n) ? bias[j] : 0.f;
+#pragma unroll
+            for (int g = 0; g < kRowGrp; ++g) {
+                const float zz = fmaf(sc, acc[g], bj);
+                if (MODE == 0) {
+                    zt[g][jl] = (j < n && g < gn) ? zz : -INFINITY;
+                } else if (j < n && g < gn) {
+                    const int64_t row = h * G + g0 + g;
+                    racc[u] = fmaf(expf(zz - row_m[row]), row_il[row], racc[u]);
+                }
+            }
+        }
+        if (MODE == 0) {
+            __syncthreads();
+            chunk_stats(zt, red, gn, h * G + g0, nchunks, ch, part_m, part_s);
+        }
+        __syncthreads();
+    }
+    if (MODE == 1) {
+        const float invG = 1.0f / (float)G;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int64_t j = j0 + tid + 256 * u;
+            if (j < n) importance[h * n + j] = racc[u] * invG;
+        }
     }
 }
 
@@ -477,7 +564,8 @@ CurveLayout curve_layout(const fw_rows &rows, void *ws) {
 
 size_t curve_ws_bytes(const fw_rows &rows) { return curve_layout(rows, nullptr).bytes; }
 
-// both logit passes of a window that k_window.hip does not take
+// both logit passes of a window that k_window.hip does not take; DC chunks of
+// 32 columns, 0: the thin kernel
 template <typename T, int DC>
 static void window_general(const fw_rows &rows, const CurveLayout &L, float *importance, hipStream_t st) {
     const int64_t H = rows.H, G = rows.G, n = rows.n;
@@ -485,13 +573,21 @@ static void window_general(const fw_rows &rows, const CurveLayout &L, float *imp
     const dim3 grid((unsigned)(H * nch));
     const T *q = (const T *)rows.q, *k = (const T *)rows.k;
     const int vec = d % (16 / (int)sizeof(T)) == 0 && ((uintptr_t)q | (uintptr_t)k) % 16 == 0;
-    const size_t lds = (size_t)4 * 64 * (DC * 2 * sizeof(T) + 4) * 4;
-    hipLaunchKernelGGL((window_logits_kernel<T, DC, 0>), grid, dim3(256), lds, st, q, k, rows.scale, rows.bias, G, n, d,
-                       nch, vec, L.part_m, L.part_s, nullptr, nullptr, nullptr);
+    const size_t lds = (size_t)4 * 64 * window_rs(DC * 2 * (int)sizeof(T)) * 4;
+    if constexpr (DC == 0)
+        hipLaunchKernelGGL((window_thin_kernel<T, 0>), grid, dim3(256), 0, st, q, k, rows.scale, rows.bias, G, n, d,
+                           nch, L.part_m, L.part_s, nullptr, nullptr, nullptr);
+    else
+        hipLaunchKernelGGL((window_logits_kernel<T, DC, 0>), grid, dim3(256), lds, st, q, k, rows.scale, rows.bias, G,
+                           n, d, nch, vec, L.part_m, L.part_s, nullptr, nullptr, nullptr);
     hipLaunchKernelGGL(window_combine_kernel, dim3((unsigned)((H * G + 255) / 256)), dim3(256), 0, st, H * G, nch,
                        L.part_m, L.part_s, L.row_m, L.row_il);
-    hipLaunchKernelGGL((window_logits_kernel<T, DC, 1>), grid, dim3(256), lds, st, q, k, rows.scale, rows.bias, G, n, d,
-                       nch, vec, nullptr, nullptr, L.row_m, L.row_il, importance);
+    if constexpr (DC == 0)
+        hipLaunchKernelGGL((window_thin_kernel<T, 1>), grid, dim3(256), 0, st, q, k, rows.scale, rows.bias, G, n, d,
+                           nch, nullptr, nullptr, L.row_m, L.row_il, importance);
+    else
+        hipLaunchKernelGGL((window_logits_kernel<T, DC, 1>), grid, dim3(256), lds, st, q, k, rows.scale, rows.bias, G,
+                           n, d, nch, vec, nullptr, nullptr, L.row_m, L.row_il, importance);
 }
 
 template <typename T>
@@ -502,12 +598,18 @@ static hipError_t curve_impl(const fw_rows &rows, float *importance, float *curv
     if (window_mfma_supported(rows)) {
         // bf16, d = 128, up to 64 window rows: MFMA scores (k_window.hip)
         launch_window_mfma(rows, L.part_m, L.part_s, L.row_m, L.row_il, importance, st);
-    } else if (rows.d <= 64) {
-        window_general<T, 2>(rows, L, importance, st);
-    } else if (rows.d <= 128) {
-        window_general<T, 4>(rows, L, importance, st);
-    } else {
-        window_general<T, 8>(rows, L, importance, st);
+    } else if (rows.d < thin_cols<T>()) {
+        window_general<T, 0>(rows, L, importance, st);
+    } else {  // as little padding as chunks of 32 and, past 128, 64 columns allow
+        switch ((rows.d + 31) / 32) {
+            case 1: window_general<T, 1>(rows, L, importance, st); break;
+            case 2: window_general<T, 2>(rows, L, importance, st); break;
+            case 3: window_general<T, 3>(rows, L, importance, st); break;
+            case 4: window_general<T, 4>(rows, L, importance, st); break;
+            case 5:
+            case 6: window_general<T, 6>(rows, L, importance, st); break;
+            default: window_general<T, 8>(rows, L, importance, st); break;
+        }
     }
     if (order)
         hipLaunchKernelGGL((unit_sort_kernel<true>), dim3((unsigned)H), dim3(kSortThreads), 0, st,

@@ -268,6 +268,25 @@ def test_general_window_edges(torch_fw, dtype, H, G, n, d, shift):
         assert np.allclose(t2np(out["curve"])[h], want, rtol=1e-6, atol=1e-12)
 
 
+@pytest.mark.parametrize("dtype,d,wide", [
+    ("f32", 15, 16), ("bf16", 23, 24),    # a key per thread below
+    ("f32", 7, 33), ("bf16", 32, 65),     # one, two and three chunks of 32 columns
+    ("f32", 96, 97), ("bf16", 97, 129),   # three, four and six
+    ("f32", 130, 193), ("bf16", 192, 256),
+])
+def test_window_column_layouts_agree(torch_fw, dtype, d, wide):
+    """Zero columns change no sum, so rows widened by them give the same bits
+    on another layout of the general pass."""
+    torch, fw = torch_fw
+    rows = W.window_rows(58, d, 2, 19, 530, d, dtype)
+    dev = fw.upload(rows)
+    pad = {k: torch.nn.functional.pad(dev[k], (0, wide - d)) for k in ("q", "k")}
+    out = fw.dropped_mass_curve(dev["q"], dev["k"], dev["scale"], dev["bias"])
+    out2 = fw.dropped_mass_curve(pad["q"], pad["k"], dev["scale"], dev["bias"])
+    for name in ("importance", "curve", "order"):
+        assert same_bits(t2np(out[name]), t2np(out2[name])), name
+
+
 @pytest.mark.parametrize("kernel", [1, 3, 7])
 def test_maxpool_scores(torch_fw, kernel):
     """SnapKV's pooling against the oracle, bit for bit (a max of float32
