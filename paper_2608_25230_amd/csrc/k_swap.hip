@@ -1156,12 +1156,14 @@ swap_bound_kernel(int64_t n, int kk, int jn, SwapState s) {
     auto pass = [&](const float4 &b, int q) __attribute__((always_inline)) {
         return fmaf(m2u[q], b.z, fmaf(m2r[q], b.y, b.x)) <= ci[q];
     };
+    // kept keys (infinite B_j) and those past the row's end are NaN here: no test
+    // passes, also where g . u_i overflowed and the right-hand side is infinite
     const int len = (int)(j1 - j0 + 63) & ~63;  // whole waves of keys
     for (int u = tid; u < len; u += BT) {
-        float4 e = make_float4(INFINITY, 0.f, 0.f, 0.f);
+        float4 e = make_float4(NAN, 0.f, 0.f, 0.f);
         if (j0 + u < j1) {
-            const float pj = pr[j0 + u];
-            e = make_float4(bj[j0 + u] - ubf * pj * pj, rj[j0 + u], pj, 0.f);
+            const float pj = pr[j0 + u], b = bj[j0 + u];
+            e = make_float4(b < INFINITY ? b - ubf * pj * pj : NAN, rj[j0 + u], pj, 0.f);
         }
         tile[u] = e;
         float mb = e.x, mr = e.x < INFINITY ? e.y : 0.f, mp = e.x < INFINITY ? e.z : 0.f;
@@ -1193,7 +1195,8 @@ swap_bound_kernel(int64_t n, int kk, int jn, SwapState s) {
                     continue;
                 }
             }
-            const float4 sl = slice[u0 / kSwapSL];            bool hs = false;
+            const float4 sl = slice[u0 / kSwapSL];
+            bool hs = false;
 #pragma unroll
             for (int q = 0; q < KT; ++q) hs |= pass(sl, q);
             if (!__ballot(hs)) continue;

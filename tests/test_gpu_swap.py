@@ -117,6 +117,26 @@ def test_long_rows_fp32_and_zero_iters(torch_fw):
     assert np.all(outn["n_swaps"] == 0) and np.all(outn["gap_traj"][..., 0] < 1e-6)
 
 
+@pytest.mark.parametrize("n", [65, 100, 128, 1100])
+def test_products_past_float32(torch_fw, n):
+    """Values whose products g . u_i overflow float32 while every norm fits: the
+    bound of such a kept key excludes nothing, and only dropped keys of the row
+    (not kept ones, nor the padding of the last tile) may be scored with it."""
+    torch, fw = torch_fw
+    p = np.zeros(n)
+    p[:3], p[3:6] = [0.3, 0.29, 0.31], [0.012, 0.011, 0.013]
+    p[6:] = (1 - p.sum()) / (n - 6)
+    v = np.zeros((1, n, 4))
+    v[0, :3, 0] = np.array([0.8, 0.78, 0.82]) * 1e19 / p[:3]
+    v[0, 3:6, 0] = -np.array([0.81, 0.79, 0.80]) * 1e19 / p[3:6]
+    v[0, 6:, 1] = np.linspace(-1, 1, n - 6) * 1e18
+    rows = W.Rows("f32", np.zeros((1, 2, 4), np.float32), np.zeros((1, n, 4), np.float32), v.astype(np.float32),
+                  np.ones(1, np.float32), np.log(p).astype(np.float32))
+    out = _run(torch, fw, rows, 3, 1)
+    assert np.all(out["n_swaps"] == 1)
+    _check(rows, 3, 1, out, [(0, 0), (0, 1)], method="gform", min_exact=1.0)
+
+
 @pytest.mark.parametrize("dtype,G,n,d,k", [
     ("f32", 1, 65, 7, 64),       # one kept-key wave, element loads, one row tile
     ("f32", 17, 301, 64, 65),    # two row tiles, two kept-key waves
