@@ -151,12 +151,10 @@ struct SwapState {
     double *ub;      // [R][2]   upper bound on the best pair value (and a spare slot)
     int64_t *ubp;    // [R]      the pair that gave the upper bound
     int32_t *cnt;    // [R]      surviving pairs
-    int32_t *fb;     // [R]      1: survivors overflowed, the full sweep runs
     int32_t *fbl;    // [R]      the rows whose survivors overflowed, in any order
     int32_t *fbn;    // [1]      their count (cleared by the init and apply passes)
     int64_t *cand;   // [R][kSwapCand] surviving pairs i 2^32 + j
-    int32_t *ord;    // [R][k]    kept keys in the bound pass's order (k <= kSwapSort)
-    float4 *kd;      // [R][k]    per kept key in that order: its bound-test terms and index
+    float4 *kd;      // [R][k]    kept keys in the bound pass's order: bound-test terms, index (k <= kSwapSort)
     int a_all;       // a is written for every key (else for the kept keys only: the
                      // MFMA sweep reads B_j from bj instead)
     int nblk;
@@ -211,7 +209,7 @@ swap_init_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, int kk, S
     __shared__ int scan[4];
     const int tid = threadIdx.x, NT = blockDim.x;
     const int64_t r = blockIdx.x, h = r / G;
-    if (s.fbn && r == 0 && tid == 0) *s.fbn = 0;
+    if (r == 0 && tid == 0) *s.fbn = 0;
     const T *vh = v + h * n * d;
     const float m = s.row_m[r], inv_l = 1.0f / s.row_l[r];
     const uint32_t key = s.thr_key[r];
@@ -527,17 +525,11 @@ swap_dots_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, int vec, 
     }
 }
 
-// The rows a sweep workgroup takes: blockIdx.y over every active row, or,
-// under the pruned search, the listed rows whose survivors overflowed,
-// gridDim.y of them at a time (so that a sweep with no such row costs a
-// small grid, not one workgroup per tile of every row).
+// The rows a sweep workgroup takes: the listed rows whose survivors
+// overflowed, gridDim.y of them at a time (so that a sweep with no such row
+// costs a small grid, not one workgroup per tile of every row).
 template <typename F>
 __device__ __forceinline__ void sweep_rows(const SwapState &s, F &&body) {
-    if (!s.fbl) {
-        const int64_t r = blockIdx.y;
-        if (s.st[r * 2]) body(r);
-        return;
-    }
     const int nfb = *s.fbn;
     for (int yy = blockIdx.y; yy < nfb; yy += gridDim.y) {
         const int64_t r = s.fbl[yy];
@@ -547,9 +539,7 @@ __device__ __forceinline__ void sweep_rows(const SwapState &s, F &&body) {
 }
 
 // The per-key records of the full sweep, (B_j or +inf if kept, p_j, 2 w_j,
-// P + p_j), for the rows the fallback sweep takes: under the pruned search
-// the dots pass does not write them for every row (they are the same values
-// it would have written).
+// P + p_j), for the rows the fallback sweep takes.
 __global__ void __launch_bounds__(256) swap_jd_kernel(int64_t n, SwapState s) {
     sweep_rows(s, [&](int64_t r) {
         const float P = (float)s.sc[r * 4 + 0];
@@ -1009,7 +999,7 @@ swap_ub_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, int kk, Swa
         s.ubp[r] = pidx;
         s.cnt[r] = 0;
     }
-    if (!s.ord) return;
+    if (!s.kd) return;
     // Order the kept keys for the bound pass by how readily their pairs pass
     // a slice test (largest first), so that the few that do share waves and
     // the other waves skip whole slices: kappa_i = c_i + 2 r_i rt + 2 UB Pi pt
@@ -1084,7 +1074,6 @@ swap_ub_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, int kk, Swa
         if (tid + 256 * x >= kk) continue;
         const int32_t i = Sl[tid + 256 * x];
         const int t = atomicAdd(&bins[bin(kv[x])], 1);
-        s.ord[r * kk + t] = i;
         const double bqi = (double)bq[i];
         const double Ai = g2 + bqi - 2.0 * (double)a[i];
         const double Pi = P - (double)p[i];
@@ -1248,13 +1237,9 @@ swap_cand_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, SwapState
     const int tid = threadIdx.x, NT = blockDim.x;
     const int cnt = s.cnt[r];
     if (cnt > kSwapCand) {  // overflow: the full sweep decides this row
-        if (tid == 0) {
-            s.fb[r] = 1;
-            s.fbl[atomicAdd(s.fbn, 1)] = (int32_t)r;
-        }
+        if (tid == 0) s.fbl[atomicAdd(s.fbn, 1)] = (int32_t)r;
         return;
     }
-    if (tid == 0) s.fb[r] = 0;
     for (int c = tid; c < d; c += NT) {
         gs[c] = s.g[r * d + c];
         ms[c] = s.mu[r * d + c];
@@ -1300,7 +1285,7 @@ swap_apply_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, int kk, 
     __shared__ double redd[256];
     __shared__ int decide;
     const int64_t r = blockIdx.x;
-    if (s.fbn && r == 0 && threadIdx.x == 0) *s.fbn = 0;  // the sweep that read it is done
+    if (r == 0 && threadIdx.x == 0) *s.fbn = 0;  // the sweep that read it is done
     if (!s.st[r * 2]) return;
     const int tid = threadIdx.x;
     float bv = INFINITY;
@@ -1455,14 +1440,10 @@ SwapLayout swap_layout(const fw_rows &rows, int k, void *ws) {
     L.s.ub = (double *)take(R * 2 * 8);
     L.s.ubp = (int64_t *)take(R * 8);
     L.s.cnt = (int32_t *)take(R * 4);
-    L.s.fb = (int32_t *)take(R * 4);
     L.s.fbl = (int32_t *)take(R * 4);
     L.s.fbn = (int32_t *)take(16);
     L.s.cand = (int64_t *)take(R * (size_t)kSwapCand * 8);
-    if (k <= kSwapSort) {
-        L.s.ord = (int32_t *)take(R * (size_t)k * 4);
-        L.s.kd = (float4 *)take(R * (size_t)k * 16);
-    }
+    if (k <= kSwapSort) L.s.kd = (float4 *)take(R * (size_t)k * 16);
     // the dots pass writes a only for the kept keys when the fallback sweep
     // is the MFMA one (it takes B_j from bj); the float sweep reads a[j]
     L.s.a_all = swap_mfma_ok(rows) ? 0 : 1;
