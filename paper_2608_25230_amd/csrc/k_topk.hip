@@ -499,7 +499,12 @@ __device__ __forceinline__ void tier_gaps(const KsArg &ks, int64_t R, int64_t r,
 // them again on the vector unit, each key into its own tier only.
 //
 // Columns are taken in slices of 16 CPL: CPL = 8 up to four tiers, else 4
-// (accumulators: 4 NT CPL registers).
+// (accumulators: 4 NT CPL registers; past 256 registers the weights spill, while
+// each slice forms the weights again).  Four tiers at 8 spill 72 registers and
+// pay only for bf16 rows of whole chunks: 64 units of 17 rows of 20,000 keys, 8
+// against 4, a call: bf16 of 128 columns 508 us and 518 (few rows 83 and 78), of
+// 100 1172 and 898, float32 of 102 1103 and 974.  Three tiers: float32 of 128
+// columns 569 and 629.
 //
 // 64 units of 4 rows of 5003 keys, four tiers: 52 us (4.4 ms with one wave per
 // row walking the keys); 8 units of 128 rows of 32,768 keys, two tiers: 90 us
@@ -597,6 +602,13 @@ tiers_kernel(TierArgs a) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const T *row = vh + (j0 + e) * d;
+                    zz[e] = (there && j0 + e < n) ? zr[j0 + e] : 0.f;
+                    // one load at any alignment, not CPL: rows of 250 columns 1926 to
+                    // 1640 us (64 units of 17 rows of 20,000 keys)
+                    if (B16 && j0 + e < n && col + CPL <= d) {
+                        __builtin_memcpy(&raw[e][0], row + col, CPL * sizeof(T));
+                        continue;
+                    }
                     uint32_t x[CPL];
 #pragma unroll
                     for (int i = 0; i < CPL; ++i) {
@@ -614,7 +626,6 @@ tiers_kernel(TierArgs a) {
 #pragma unroll
                         for (int i = 0; i < CPL; ++i) to[i] = x[i];
                     }
-                    zz[e] = (there && j0 + e < n) ? zr[j0 + e] : 0.f;
                 }
             }
             float p[8];
@@ -937,7 +948,7 @@ static void tiers_nt(const TierArgs &a, hipStream_t st) {
     switch (a.ks.n) {
         case 1: wide ? tiers_t<T, 8, 2>(a, st) : tiers_t<T, 4, 2>(a, st); break;
         case 2: wide ? tiers_t<T, 8, 3>(a, st) : tiers_t<T, 4, 3>(a, st); break;
-        case 3: wide ? tiers_t<T, 8, 4>(a, st) : tiers_t<T, 4, 4>(a, st); break;
+        case 3: wide && sizeof(T) == 2 && a.vec ? tiers_t<T, 8, 4>(a, st) : tiers_t<T, 4, 4>(a, st); break;
         case 4: tiers_t<T, 4, 5>(a, st); break;
         case 5: tiers_t<T, 4, 6>(a, st); break;
         case 6: tiers_t<T, 4, 7>(a, st); break;

@@ -39,6 +39,8 @@ def _run(torch, fw, rows, ks, shift=0):
     ("bf16", 5, 300, 100, (7, 150), 0),           # d no multiple of 8: element loads
     ("bf16", 6, 301, 64, (7, 150), 1),            # unaligned operands
     ("bf16", 3, 200, 160, tuple(range(5, 45, 5)), 0),  # eight budgets, three slices of 64
+    ("bf16", 18, 333, 140, (4, 40, 200), 1),      # three budgets in slices of 64, chunks at odd addresses
+    ("f32", 9, 290, 104, (4, 40, 200), 0),        # the same on float32, 16-byte loads
     ("f32", 1, 1, 1, (1,), 0),
     ("f32", 16, 64, 64, (16, 64), 0),
     ("f32", 90, 1999, 64, (64, 250, 999), 0),
