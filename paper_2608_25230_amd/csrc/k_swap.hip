@@ -1231,7 +1231,7 @@ swap_bound_kernel(int64_t n, int kk, int jn, SwapState s) {
 // the survivors (and the upper bound's own pair) evaluated exactly; the
 // winner goes to the first partial slot of the row, the others are cleared
 template <typename T>
-__global__ void __launch_bounds__(kSwapCandT)
+__global__ void __launch_bounds__(kSwapCandT) __attribute__((amdgpu_waves_per_eu(4, 4)))
 swap_cand_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, SwapState s) {
     __shared__ double redv[kSwapCandT / 64];
     __shared__ int64_t redi[kSwapCandT / 64];
