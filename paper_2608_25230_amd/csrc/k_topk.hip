@@ -878,11 +878,16 @@ static void scores_t(const T *q, const T *k, const float *scale, const float *bi
 template <typename T>
 static void scores_dc(const T *q, const T *k, const float *scale, const float *bias, int64_t H, int64_t G, int64_t n,
                       int d, float *z, hipStream_t st) {
-    // row tiles per wave: four where the query operands fit the registers
-    const bool many = G > 16;
-    if (d <= 64) many ? scores_t<T, 2, 4>(q, k, scale, bias, H, G, n, d, z, st) : scores_t<T, 2, 1>(q, k, scale, bias, H, G, n, d, z, st);
-    else if (d <= 128) many ? scores_t<T, 4, sizeof(T) == 2 ? 4 : 2>(q, k, scale, bias, H, G, n, d, z, st) : scores_t<T, 4, 1>(q, k, scale, bias, H, G, n, d, z, st);
-    else if (sizeof(T) == 2 && many) scores_t<T, 8, 2>(q, k, scale, bias, H, G, n, d, z, st);
+    // Row tiles per wave: two past 16 rows, so that a key tile turned through LDS
+    // serves both; where they don't fit the registers (float32 past 128 columns),
+    // one.  A call with one, two and four tiles, bf16 of 128 columns: 64 units of
+    // 24 rows of 8192 keys 144, 144 and 179 us (four are mostly padding), 32 of 128
+    // rows 258, 247 and 253; float32 of 64 columns 272, 254 and 259.  Least gain:
+    // 16 units of 48 rows of 8192 bf16 keys 94, 98 and 105.
+    const bool two = G > 16;
+    if (d <= 64) two ? scores_t<T, 2, 2>(q, k, scale, bias, H, G, n, d, z, st) : scores_t<T, 2, 1>(q, k, scale, bias, H, G, n, d, z, st);
+    else if (d <= 128) two ? scores_t<T, 4, 2>(q, k, scale, bias, H, G, n, d, z, st) : scores_t<T, 4, 1>(q, k, scale, bias, H, G, n, d, z, st);
+    else if (sizeof(T) == 2 && two) scores_t<T, 8, 2>(q, k, scale, bias, H, G, n, d, z, st);
     else scores_t<T, 8, 1>(q, k, scale, bias, H, G, n, d, z, st);
 }
 
@@ -902,8 +907,17 @@ hipError_t launch_select(const float *z, int64_t R, int64_t n, const KsArg &ks, 
     int cap = kSelList;
     if (topk_idx) cap = kmax + kSelList / 2 > sort_len ? kmax + kSelList / 2 : sort_len;
     const size_t lds = (size_t)cap * sizeof(unsigned long long);
-    // long rows, and few rows, on 16 waves: a row's passes are one chain per thread
-    const bool big = (n > 8192 && R <= 65536) || (n > 2048 && R < 1024);
+    // 16 waves for up to a row per CU, where a row's passes are one chain per
+    // thread, and for rows that four don't hold in registers (8192 logits); with
+    // many rows, whose barriers then bound it, only from where reading them again
+    // costs more, sooner when long index lists are ranked.  A call with four and 16
+    // waves: 256 rows of 2500 logits 32 and 30 us, of 8192 51 and 44; 512 of 2500 38
+    // and 41, of 8192 66 and 67, of 12,000 106 and 86; 8192 rows of 8200 438 and 568,
+    // of 12,288 655 and 742 (3072 indices: 1056 and 927), of 16,384 893 and 920, of
+    // 32,768 1779 and 1603 (8192 indices: 6637 and 2522).
+    const bool list = topk_idx && kmax >= 1024;
+    // (a grid's threads are counted in 32 bits)
+    const bool big = n > (R <= 256 ? 2048 : R <= 768 ? 8192 : list ? 9216 : 12288) && R < ((int64_t)1 << 22);
 #define FW_SELECT(NTH, PER)                                                                                        \
     hipLaunchKernelGGL((select_kernel<NTH, PER>), dim3((unsigned)R), dim3(NTH), lds, st, z, R, n, ks, row_m, row_l, \
                        thr_key, thr_cut, topk_idx, kmax, sort_len, cap)

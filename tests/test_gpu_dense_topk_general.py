@@ -66,6 +66,27 @@ def test_long_rows_select(torch_fw, n):
     _compare(rows, ks, out, _oracle_rows(rows, ks), torch, zg)
 
 
+@pytest.mark.parametrize("H,n,ks", [
+    (32, 2100, (9, 500)),    # a row per CU: 16 waves
+    (33, 2100, (9, 500)),    # past that four, 32 logits per thread
+    (97, 8300, (1000, 3)),   # past 768 rows four waves read them again
+    (97, 9300, (1024, 3)),   # 16 with a long index list
+])
+def test_many_rows_select(torch_fw, H, n, ks):
+    """The selection's waves by rows, length and list: the rank order of the
+    GPU's own logits, and the largest budget's dropped mass."""
+    torch, fw = torch_fw
+    rows = W.sink_rows(75, H, H, 8, n, 8, "f32", sink=4.0)
+    out, zg = _run(torch, fw, rows, ks)
+    want = np.argsort(-zg, axis=1, kind="stable")[:, :max(ks)]
+    assert np.array_equal(t2np(out["topk_idx"]).reshape(H * 8, -1), want)
+    p = np.exp(zg.astype(np.float64) - zg.max(axis=1, keepdims=True))
+    p /= p.sum(axis=1, keepdims=True)
+    kept = np.take_along_axis(p, want, axis=1).sum(axis=1)
+    t = int(np.argmax(ks))
+    assert np.allclose(t2np(out["dropped"])[t].reshape(-1), 1.0 - kept, rtol=1e-4, atol=1e-6)
+
+
 @pytest.mark.parametrize("case", ["outlier", "equal", "masked", "lowest"])
 def test_selection_falls_back(torch_fw, case):
     """Rows whose histogram puts more logits into one bin than rank counting
