@@ -382,14 +382,15 @@ swap_init_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, int kk, S
     }
 }
 
-// a_j = g . u_j = p_j (v_j . g - mu . g) for every key, and from it B_j; up to
-// RT tiles of 16 rows of a unit per wave, so each key's values are read once
-// for them.  v_j . g is a float32 sum in column order: the float32 MFMA chain
+// a_j = g . u_j = p_j (v_j . g - mu . g) for every key, and from it B_j; a
+// tile of 16 rows of a unit per wave, so each key's values are read once for
+// them (two tiles measured 0 to 9 % slower a call: 4 units of 32 rows of 2001
+// keys 423 and 449 us, 16 of 64 rows of 32,768 15.1 and 15.3 ms).  v_j . g is a float32 sum in column order: the float32 MFMA chain
 // of the top-k logits (lane (m, kg) feeds columns kg, 4 + kg, ...; see
 // scores_kernel), g rounded to float32 in registers.  Bound by the per-key
 // arrays (13 bytes per row and key).  1024 rows of 32,768 keys: 233 us, 401 us
 // with one thread per key and g read from LDS.
-template <typename T, int DC, int RT>
+template <typename T, int DC>
 __global__ void __launch_bounds__(256)
 swap_dots_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, int vec, SwapState s) {
     constexpr bool B16 = sizeof(T) == 2;
@@ -399,18 +400,18 @@ swap_dots_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, int vec, 
     constexpr int RS = CH + 4;              // words per row and kg: no bank conflicts on the reads
     constexpr int PW = B16 ? 2 : 1;         // columns per word
     __shared__ __align__(16) uint32_t lds_v[4 * 64 * RS];
-    __shared__ double mgs[16 * RT];
+    __shared__ double mgs[16];
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint32_t *tile = lds_v + w * (64 * RS);
-    const uint32_t rgs = (uint32_t)((G + 16 * RT - 1) / (16 * RT));
-    const int64_t h = blockIdx.y / rgs, g0 = (int64_t)(blockIdx.y % rgs) * (16 * RT);
-    const int rows = G - g0 < 16 * RT ? (int)(G - g0) : 16 * RT;
+    const uint32_t rgs = (uint32_t)((G + 15) / 16);
+    const int64_t h = blockIdx.y / rgs, g0 = (int64_t)(blockIdx.y % rgs) * 16;
+    const int rows = G - g0 < 16 ? (int)(G - g0) : 16;
     const int64_t r0 = h * G + g0;
     const T *vh = v + h * n * (int64_t)d;
     const int m16 = lane & 15, kg = lane >> 4;
     // mu . g per row: 16 lanes per row, their partial sums added by a butterfly
-    for (int rr0 = 0; rr0 < 16 * RT; rr0 += 16) {
-        const int rr = rr0 + (tid >> 4), ln = tid & 15;
+    {
+        const int rr = tid >> 4, ln = tid & 15;
         double mg = 0.0;
         if (rr < rows)
             for (int c = ln; c < d; c += 16) mg += s.mu[(r0 + rr) * d + c] * s.g[(r0 + rr) * d + c];
@@ -418,26 +419,18 @@ swap_dots_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, int vec, 
         for (int off = 1; off < 16; off <<= 1) mg += __shfl_xor(mg, off);
         if (ln == 0) mgs[rr] = mg;
     }
-    float gf[RT][LD * 4 * PW];
-    bool act[RT];
+    float gf[LD * 4 * PW];
+    const bool act = m16 < rows && s.st[(r0 + m16) * 2];
 #pragma unroll
-    for (int x = 0; x < RT; ++x) {
-        const int rr = 16 * x + m16;
-        act[x] = rr < rows && s.st[(r0 + rr) * 2];
+    for (int c = 0; c < CH; ++c) {
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-#pragma unroll
-            for (int y = 0; y < PW; ++y) {
-                const int col = E * c + 4 * y + kg;
-                gf[x][c * PW + y] = (act[x] && col < d) ? (float)s.g[(r0 + rr) * d + col] : 0.f;
-            }
+        for (int y = 0; y < PW; ++y) {
+            const int col = E * c + 4 * y + kg;
+            gf[c * PW + y] = (act && col < d) ? (float)s.g[(r0 + m16) * d + col] : 0.f;
         }
     }
     __syncthreads();
-    bool any = false;
-#pragma unroll
-    for (int x = 0; x < RT; ++x) any |= act[x];
-    if (!__ballot(any)) return;  // every row of the group has stopped (the same on each wave)
+    if (!__ballot(act)) return;  // every row of the tile has stopped (the same on each wave)
     uint4 raw[LD];
     auto load = [&](int64_t t) {
 #pragma unroll
@@ -475,9 +468,7 @@ swap_dots_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, int vec, 
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         if (t + step < tiles) load(t + step);
-        f32x4 acc[RT];
-#pragma unroll
-        for (int x = 0; x < RT; ++x) acc[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int f = 0; f < LD; ++f) {
             const uint4 kf = mine[f];
@@ -487,39 +478,34 @@ swap_dots_kernel(const T *__restrict__ v, int64_t G, int64_t n, int d, int vec, 
 #pragma unroll
                 for (int y = 0; y < PW; ++y) {
                     const float kv = __uint_as_float(!B16 ? kw[c] : y ? kw[c] & 0xFFFF0000u : kw[c] << 16);
-#pragma unroll
-                    for (int x = 0; x < RT; ++x)
-                        acc[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv, gf[x][(4 * f + c) * PW + y], acc[x], 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kv, gf[(4 * f + c) * PW + y], acc, 0, 0, 0);
                 }
             }
         }
-        // lane: row m16 of each row tile, keys 4 kg .. 4 kg + 3
+        // lane: row m16, keys 4 kg .. 4 kg + 3
         const int64_t j = 16 * t + 4 * kg;
+        if (!act) continue;
+        const int64_t at = (r0 + m16) * n + j;
+        const double mg = mgs[m16];
+        if (j + 4 <= n) {
+            const f32x4u pj = *(const f32x4u *)(s.p + at), bq = *(const f32x4u *)(s.bq + at);
+            uint32_t in;
+            __builtin_memcpy(&in, s.inS + at, 4);
+            f32x4u b;
 #pragma unroll
-        for (int x = 0; x < RT; ++x) {
-            if (!act[x]) continue;
-            const int64_t at = (r0 + 16 * x + m16) * n + j;
-            const double mg = mgs[16 * x + m16];
-            if (j + 4 <= n) {
-                const f32x4u pj = *(const f32x4u *)(s.p + at), bq = *(const f32x4u *)(s.bq + at);
-                uint32_t in;
-                __builtin_memcpy(&in, s.inS + at, 4);
-                f32x4u b;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float aj = pj[i] * (float)((double)acc[x][i] - mg);
-                    const bool kept = (in >> (8 * i)) & 1u;
-                    if (kept || s.a_all) s.a[at + i] = aj;
-                    b[i] = kept ? INFINITY : bq[i] + 2.f * aj;
-                }
-                *(f32x4u *)(s.bj + at) = b;
-            } else {
-                for (int i = 0; i < 4 && j + i < n; ++i) {
-                    const float aj = s.p[at + i] * (float)((double)acc[x][i] - mg);
-                    const bool kept = s.inS[at + i];
-                    if (kept || s.a_all) s.a[at + i] = aj;
-                    s.bj[at + i] = kept ? INFINITY : s.bq[at + i] + 2.f * aj;
-                }
+            for (int i = 0; i < 4; ++i) {
+                const float aj = pj[i] * (float)((double)acc[i] - mg);
+                const bool kept = (in >> (8 * i)) & 1u;
+                if (kept || s.a_all) s.a[at + i] = aj;
+                b[i] = kept ? INFINITY : bq[i] + 2.f * aj;
+            }
+            *(f32x4u *)(s.bj + at) = b;
+        } else {
+            for (int i = 0; i < 4 && j + i < n; ++i) {
+                const float aj = s.p[at + i] * (float)((double)acc[i] - mg);
+                const bool kept = s.inS[at + i];
+                if (kept || s.a_all) s.a[at + i] = aj;
+                s.bj[at + i] = kept ? INFINITY : s.bq[at + i] + 2.f * aj;
             }
         }
     }
@@ -1468,33 +1454,36 @@ size_t swap_ws_bytes(const fw_rows &rows, int k, int max_iters) {
     return swap_layout(rows, k, nullptr).bytes;
 }
 
-template <typename T, int DC, int RT>
+template <typename T, int DC>
 static void dots_t(const T *v, int64_t H, int64_t G, int64_t n, int d, const SwapState &s, hipStream_t st) {
-    const int64_t groups = H * ((G + 16 * RT - 1) / (16 * RT)), tiles = (n + 15) / 16;
+    const int64_t groups = H * ((G + 15) / 16), tiles = (n + 15) / 16;
     // about eight workgroups per CU, and no fewer than one tile per wave
     int64_t bx = (2048 + groups - 1) / groups;
     if (bx > (tiles + 3) / 4) bx = (tiles + 3) / 4;
     const int vec = d % (16 / (int)sizeof(T)) == 0 && (uintptr_t)v % 16 == 0;
-    hipLaunchKernelGGL((swap_dots_kernel<T, DC, RT>), dim3((unsigned)bx, (unsigned)groups), dim3(256), 0, st, v, G, n, d,
-                       vec, s);
+    hipLaunchKernelGGL((swap_dots_kernel<T, DC>), dim3((unsigned)bx, (unsigned)groups), dim3(256), 0, st, v, G, n, d, vec,
+                       s);
 }
 
-// row tiles per wave: two where there are rows for them and g's registers fit
 template <typename T>
 static void launch_dots(const T *v, int64_t H, int64_t G, int64_t n, int d, const SwapState &s, hipStream_t st) {
-    if (d <= 64) G > 16 ? dots_t<T, 2, 2>(v, H, G, n, d, s, st) : dots_t<T, 2, 1>(v, H, G, n, d, s, st);
-    else if (d <= 128) G > 16 ? dots_t<T, 4, 2>(v, H, G, n, d, s, st) : dots_t<T, 4, 1>(v, H, G, n, d, s, st);
-    else dots_t<T, 8, 1>(v, H, G, n, d, s, st);
+    if (d <= 64) dots_t<T, 2>(v, H, G, n, d, s, st);
+    else if (d <= 128) dots_t<T, 4>(v, H, G, n, d, s, st);
+    else dots_t<T, 8>(v, H, G, n, d, s, st);
 }
 
 // Kept keys per workgroup: no more than there are (a wave of absent keys still
 // walks the slices; 120 rows of 128 kept keys of 2001: 30 us, 149 with four per
 // thread); four per thread for many, so that each staged key serves four tests.
-// Keys per workgroup: 1024, or 256 where the rows alone do not fill the chip.
+// Keys per workgroup: 256, or 1024 for long rows (a workgroup's kept keys are
+// read once for more) unless the rows alone do not fill the chip.  Three sweeps
+// with 256 and 1024: 512 rows of 5000 bf16 keys, 400 kept, 1.44 and 1.62 ms, of
+// 8192, 800 kept, 2.24 and 2.38; of 10,000, 500 kept, 2.95 and 2.77; 68 rows of
+// 10,000 1.57 and 1.73.
 static void launch_bound(int64_t R, int64_t n, int k, const SwapState &s, hipStream_t st) {
     const int kb = k <= 64 ? 64 : k <= 128 ? 128 : k <= 256 ? 256 : k <= 512 ? 512 : 1024;
     const int64_t nic = (k + kb - 1) / kb;
-    const int jn = R * nic * ((n + kSwapJC - 1) / kSwapJC) >= 2048 ? kSwapJC : 256;
+    const int jn = n > 8192 && R * nic * ((n + kSwapJC - 1) / kSwapJC) >= 2048 ? kSwapJC : 256;
     const dim3 g((unsigned)(nic * ((n + jn - 1) / jn)), (unsigned)R);
     const size_t lds = (size_t)(jn + jn / kSwapSL + jn / 64) * sizeof(float4);
     switch (kb) {
