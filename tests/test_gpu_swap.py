@@ -117,6 +117,21 @@ def test_long_rows_fp32_and_zero_iters(torch_fw):
     assert np.all(outn["n_swaps"] == 0) and np.all(outn["gap_traj"][..., 0] < 1e-6)
 
 
+@pytest.mark.parametrize("dtype,n,d,k", [("f32", 200, 64, 20), ("bf16", 1024, 128, 100), ("bf16", 130, 20, 9)])
+def test_operands_off_alignment(torch_fw, dtype, n, d, k):
+    """q, k and v one element past a 16-byte boundary: the same bits."""
+    torch, fw = torch_fw
+    rows = W.sink_rows(43, n, 2, 3, n, d, dtype, sink=4.0)
+    dev = fw.upload(rows)
+    out = fw.swap(dev["q"], dev["k"], dev["v"], k, 6, dev["scale"], dev["bias"])
+    off = {x: torch.empty(dev[x].numel() + 1, dtype=dev[x].dtype, device="cuda")[1:].view(dev[x].shape).copy_(dev[x])
+           for x in ("q", "k", "v")}
+    out2 = fw.swap(off["q"], off["k"], off["v"], k, 6, dev["scale"], dev["bias"])
+    for name in out:
+        if not name.startswith("_"):
+            assert same_bits(t2np(out[name]), t2np(out2[name])), name
+
+
 @pytest.mark.parametrize("n", [65, 100, 128, 1100])
 def test_products_past_float32(torch_fw, n):
     """Values whose products g . u_i overflow float32 while every norm fits: the

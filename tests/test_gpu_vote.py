@@ -101,6 +101,20 @@ def test_small_groups_fp32(torch_fw, cfg):
     print(cfg, t)
 
 
+@pytest.mark.parametrize("dtype,gs,n,d", [("f32", 4, 300, 64), ("bf16", 1, 300, 128), ("bf16", 2, 70, 20)])
+def test_operands_off_alignment(torch_fw, dtype, gs, n, d):
+    """q, k and v one element past a 16-byte boundary: the same bits."""
+    torch, fw = torch_fw
+    rows = W.sink_rows(78, n, 2, 2 * gs, n, d, dtype, sink=4.0)
+    dev = fw.upload(rows)
+    out = fw.group_vote(dev["q"], dev["k"], dev["v"], 9, gs, dev["scale"], dev["bias"])
+    off = {x: torch.empty(dev[x].numel() + 1, dtype=dev[x].dtype, device="cuda")[1:].view(dev[x].shape).copy_(dev[x])
+           for x in ("q", "k", "v")}
+    out2 = fw.group_vote(off["q"], off["k"], off["v"], 9, gs, dev["scale"], dev["bias"])
+    for name in out:
+        assert same_bits(t2np(out[name]), t2np(out2[name])), name
+
+
 @pytest.mark.parametrize("s", [3, 32, 40])  # the waves' lists up to 32, one team pick at a time beyond
 @pytest.mark.parametrize("gs", [1, 4, 6])   # one row; every row's weights resident; rows beyond the resident ones
 @pytest.mark.parametrize("what", ["query", "key", "mask"])
