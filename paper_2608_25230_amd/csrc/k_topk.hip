@@ -69,8 +69,8 @@ __device__ __forceinline__ uint4 chunk16(const T *row, int c, int d, bool vec) {
 // word.
 //
 // Bound by the logits' writes, the keys' reads and, with many rows, the
-// float32 MFMA rate.  64 units of 4 rows of 5003 bf16 keys: 30 us (95 us as
-// 32 x 64 tiles of vector products); 8 units of 128 rows of 32,768: 118 us (272).
+// float32 MFMA rate.  64 units of 4 rows of 5003 bf16 keys: 26 us (95 us as
+// 32 x 64 tiles of vector products); 8 units of 128 rows of 32,768: 107 us (272).
 // ---------------------------------------------------------------------------
 template <typename T, int DC, int RT>
 __global__ void __launch_bounds__(256)
@@ -496,7 +496,10 @@ __device__ __forceinline__ void tier_gaps(const KsArg &ks, int64_t R, int64_t r,
 // weight times a bf16 value in a float32 sum, as on the vector unit.  float32
 // values use the float32 MFMA.  A masked weight times an infinite or NaN value
 // would put NaN into every tier, so a wave whose sums are not finite forms
-// them again on the vector unit, each key into its own tier only.
+// them again on the vector unit, each key into its own tier only: one infinite
+// value makes the decode call below 950 us instead of 86, and 8 units of 128 rows
+// of 32,768 keys 4.7 ms instead of 0.27, with it in every unit 1.3 and 4.8 ms
+// (4.6 and 23.7 ms for any values with one wave per row walking the keys).
 //
 // Columns are taken in slices of 16 CPL: CPL = 8 up to four tiers, else 4
 // (accumulators: 4 NT CPL registers; past 256 registers the weights spill, while
@@ -506,8 +509,8 @@ __device__ __forceinline__ void tier_gaps(const KsArg &ks, int64_t R, int64_t r,
 // 100 1172 and 898, float32 of 102 1103 and 974.  Three tiers: float32 of 128
 // columns 569 and 629.
 //
-// 64 units of 4 rows of 5003 keys, four tiers: 52 us (4.4 ms with one wave per
-// row walking the keys); 8 units of 128 rows of 32,768 keys, two tiers: 90 us
+// 64 units of 4 rows of 5003 keys, four tiers: 44 us (4.4 ms with one wave per
+// row walking the keys); 8 units of 128 rows of 32,768 keys, two tiers: 89 us
 // (23.5 ms).  Bound by the load latency of the few blocks a wave has and by the
 // weights (expf and three-part splits, 600 vector instructions per block).
 template <typename T, int CPL, int NT>
@@ -936,7 +939,7 @@ hipError_t launch_select(const float *z, int64_t R, int64_t n, const KsArg &ks, 
 
 // Key splits, at least eight 32-key blocks each (two per wave).  bf16: about
 // 512 workgroups, the two per CU that run at once (64 units of 4 rows of 5003
-// keys: 52 us against 72 with 1024); float32, whose products run at a
+// keys: a quarter less than with 1024); float32, whose products run at a
 // sixteenth of the rate: about 1024 (16 units of 90 rows of 1999 keys: 35 us
 // against 42 with 512).
 int tiers_splits(int dtype, int64_t H, int64_t G, int64_t n) {

@@ -20,7 +20,7 @@
 //               gap (1 - p(S)) ||m_{S^c} - m_S||, dropped mass.
 // Rows whose selection is degenerate (all logits equal, non-finite values, or
 // more than 128 logits sharing the threshold bin) are listed and recomputed by
-// a one-row-per-workgroup fallback that selects by radix over the exact keys.
+// a one-row-per-workgroup fallback that sorts the exact keys.
 #include "fw_internal.hpp"
 #include "topk_fused.hpp"
 

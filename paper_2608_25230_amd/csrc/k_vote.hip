@@ -14,7 +14,8 @@
 // weights, of RB rows; a group of at most RB rows needs no array of summed
 // masses, and the vote keys' weights are read back instead of formed again).
 // Bound by the float64 multiply-adds and by the lanes' reductions of the
-// logits: 1536 groups of 4 rows, 4096 bf16 keys of 128 columns: 2.06 ms, 3.12 ms
+// logits, one workgroup per CU (four rows at a time spill 80 of 256 registers,
+// two 51): 1536 groups of 4 rows, 4096 bf16 keys of 128 columns: 2.08 ms, 3.12 ms
 // one row at a time.
 #include "fw_internal.hpp"
 #include "instance64.hpp"
